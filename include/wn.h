@@ -167,7 +167,9 @@ int wn_create(const wn_config* config, const wn_weights* weights, wn_handle** ou
 /*
  * Bytes of device workspace one call with B streams needs: the generator state
  * of every stream (each layer's dilation history of r fp32 values per step of
- * its dilation, the step counter and the last two samples) plus a status word.
+ * its dilation, the step counter and the last two samples) plus a status word, and
+ * the scratch of wn_teacher_force (25 MB at r = 64; a workspace without it is accepted
+ * too, and teacher forcing then goes step by step).
  * The layout is private.  Returns 0 for a null handle or B < 1.
  */
 size_t wn_workspace_bytes(const wn_handle* h, int32_t B);
@@ -204,7 +206,9 @@ int wn_generate_sampled(wn_handle* h, int32_t B, int32_t T, const float* cond, c
  * draw, and writes the pre-softmax logits of every step.
  *   y       device int32 [B][T], values 0 .. a-1 (values outside are clamped)
  *   logits  device fp32 [B][T][a] out
- * Other arguments and errors as wn_generate.
+ * Other arguments and errors as wn_generate.  With the samples given no step waits for another, so a
+ * call takes all of its steps through a layer at once (every sum in fp32; a sequence cut into calls
+ * gives the logits of one call bit for bit).  With WN_KERNEL set it goes step by step on that family.
  */
 int wn_teacher_force(wn_handle* h, int32_t B, int32_t T, const float* cond, const int32_t* y,
                      float* logits, void* workspace, size_t ws_bytes, int32_t reset, void* stream);
@@ -228,7 +232,9 @@ int wn_status(wn_handle* h, const void* workspace, void* stream);
  * whole grid leaves at a step boundary (its outputs from that step on are not written) and the
  * call's status word becomes WN_EABORTED (wn_status).  While the request stands, calls still
  * launch and stop at their first step; withdraw it before the next call, which must pass
- * reset = 1.  A call that has passed its last check finishes normally (status WN_OK).
+ * reset = 1.  A call that has passed its last check finishes normally (status WN_OK).  A
+ * wn_teacher_force call that takes its steps at once reads the word at the start of every 16384 rows
+ * (streams x steps; a few hundred microseconds of work).
  * Errors: WN_EINVAL (null handle, on not 0 or 1).  Nothing is launched.
  */
 int wn_abort(wn_handle* h, int32_t on);

@@ -2,6 +2,7 @@
 // layout and kernel selection.  Declarations and contracts are in include/wn.h.
 #include "wn.h"
 #include "wn_internal.h"
+#include "wn_teach.h"
 
 #include <algorithm>
 #include <cmath>
@@ -24,6 +25,9 @@ struct wn_handle {
   WnDevWeights w{};
   bool chain_ok = false;  // the multi-CU kernel can serve this model (fp32, supported shape)
   bool xcd_map = false;   // blocks of the multi-CU kernel's grid run on XCD (block mod 8)
+  bool teach_ok = false;  // teacher forcing takes all steps of a call at once (wn_teach.hip)
+  void* dteach = nullptr;  // its packed fp32 weights
+  WnTeachWeights teach{};
   bool group_ok = false;  // the batched MFMA kernel serves every B
   bool mchain_ok = false; // the multi-CU MFMA kernel can serve this model (bf16 or int8, supported shape)
   // WN_KERNEL at wn_create: the one kernel family calls may use ("" = the default choice); a call the
@@ -185,6 +189,26 @@ WsLayout ws_layout(const wn_handle* h, int B) {
   return l;
 }
 
+// Polls before a wait gives up (seconds of spinning); WN_SPIN_LIMIT overrides it so that tests can force
+// the timeout path from the host.
+int spin_limit() {
+  if (const char* sl = std::getenv("WN_SPIN_LIMIT")) {
+    const long v = std::strtol(sl, nullptr, 10);
+    if (v > 0 && v < (1L << 30)) return (int)v;
+  }
+  return 1 << 22;
+}
+
+// Teacher forcing takes every step of a call at once (wn_teach.hip) on a default handle; a handle that
+// WN_KERNEL binds to one family runs it there, step by step.
+bool teach_ok(const wn_handle* h) { return h->teach_ok; }
+
+// Its scratch lies behind the generator's state in the workspace.  A workspace that ends before it (no
+// larger than a handle bound to one family asks for) still serves every call, teacher forcing step by step.
+size_t teach_bytes(const wn_handle* h, int B) {
+  return teach_ok(h) ? align_up(wn_teach_scratch_bytes(h->R, B, WN_TEACH_ROWS), 256) : 0;
+}
+
 const wn_sampler kDirect = {WN_SAMPLE_DIRECT, 1.0f, WN_A};
 
 void set_sampler(WnIO& io, const wn_sampler& sp) {
@@ -218,13 +242,56 @@ int check_call(wn_handle* h, int B, int T, const void* cond, const void* a1, con
   return WN_OK;
 }
 
+// Teacher forcing of every step at once, on the state of the family that generates with B streams.
+int launch_teach(wn_handle* h, int B, int T, const float* cond, const int32_t* y_in, float* logits, const WsLayout& l,
+                 char* base, int reset, hipStream_t st) {
+  WnTeachArgs g{};
+  WnChainPlan plan;
+  const int variant = variant_for(h, B);
+  g.ring_kind = variant == WN_VARIANT_GROUP ? WN_RING_PAIR : WN_RING_F32;
+  if (variant == WN_VARIANT_MCHAIN && mchain_plan_for(h, B, &plan)) {
+    g.ring_kind = WN_RING_TILES;
+    g.ring_g = plan.G;
+    g.ring_ns = wn_mchain_columns(plan);
+  } else if (variant == WN_VARIANT_CHAIN && chain_plan_for(h, B, &plan)) {
+    g.ring_kind = WN_RING_TAGGED;
+  }
+  g.d = h->dims;
+  g.w = h->dmem_f32 ? h->w_chain : h->w;
+  g.p = h->teach;
+  g.io.cond = cond;
+  g.io.y_in = y_in;
+  g.io.logits = logits;
+  g.io.B = B;
+  g.io.T = T;
+  g.io.reset = reset;
+  g.io.init_sample = h->init_sample;
+  g.io.abort_flag = h->abort_dev;
+  g.status = reinterpret_cast<int32_t*>(base + l.status_off);
+  g.state = reinterpret_cast<int64_t*>(base + l.state_off);
+  g.ring = base + l.hist_off;
+  g.spin_limit = spin_limit();
+  if (reset) {
+    // as before a generating call: histories, mailboxes and map (none with the single-CU families)
+    const size_t bytes = l.mb_off ? (l.mb_off - l.hist_off) + (l.mb_words + WN_CHAIN_MAP_WORDS) * 8
+                                  : (size_t)B * h->dims.hist_len * sizeof(float);
+    const hipError_t e = wn_chain_reset(static_cast<unsigned long long*>(g.ring), bytes / 8, g.status, st);
+    if (e != hipSuccess) return hip_fail(e, "reset kernel launch");
+  }
+  const hipError_t e = wn_teach_launch(g, base + l.total, WN_TEACH_ROWS, st);
+  if (e != hipSuccess) return hip_fail(e, "teacher forcing launch");
+  return WN_OK;
+}
+
 int launch(wn_handle* h, int B, int T, const float* cond, const float* u, const int32_t* y_in, int32_t* y_out,
-           float* logits, void* ws, int reset, void* stream, bool teacher, const wn_sampler& sp) {
+           float* logits, void* ws, size_t ws_bytes, int reset, void* stream, bool teacher, const wn_sampler& sp) {
   DeviceScope scope(h->device);
   if (!scope.ok()) return fail(WN_EHIP, "cannot select the handle's device");
   const WsLayout l = ws_layout(h, B);
   char* base = static_cast<char*>(ws);
   hipStream_t st = static_cast<hipStream_t>(stream);
+  if (teacher && teach_ok(h) && ws_bytes >= l.total + teach_bytes(h, B))
+    return launch_teach(h, B, T, cond, y_in, logits, l, base, reset, st);
   WnChainPlan plan;
   const int variant = variant_for(h, B);
   const bool mchain = variant == WN_VARIANT_MCHAIN && mchain_plan_for(h, B, &plan);
@@ -259,13 +326,7 @@ int launch(wn_handle* h, int B, int T, const float* cond, const float* u, const 
     g.off_qtail = plan.off_qtail;
     g.nch = plan.nch;
     for (int c = 0; c <= plan.nch; ++c) g.layer_begin[c] = plan.layer_begin[c];
-    // polls before a wait gives up (seconds of spinning); WN_SPIN_LIMIT overrides it so that tests
-    // can force the timeout path from the host
-    g.spin_limit = 1 << 22;
-    if (const char* sl = std::getenv("WN_SPIN_LIMIT")) {
-      const long v = std::strtol(sl, nullptr, 10);
-      if (v > 0 && v < (1L << 30)) g.spin_limit = (int)v;
-    }
+    g.spin_limit = spin_limit();
     g.nrep = plan.nrep;
     g.G = plan.G;
     g.ub = plan.ub;
@@ -505,8 +566,8 @@ int wn_create(const wn_config* c, const wn_weights* w, wn_handle** out) {
   if (want_chain && wn_chain_supported(R, S, L) && cus >= WN_CHAIN_GRID && coop) h->chain_ok = true;
   if (want_chain && (bf || i8) && wn_mchain_supported(R, S, L) && cus >= WN_CHAIN_GRID && coop) h->mchain_ok = true;
   if (h->chain_ok || h->mchain_ok) h->xcd_map = wn_chain_xcd_map_ok();
-  if (h->chain_ok && (i8 || bf)) {
-    // fp32 copies of the matrices for the multi-CU kernel: each bf16 weight (exact in fp32), or each
+  if ((h->chain_ok || h->force.empty()) && (i8 || bf)) {
+    // fp32 copies of the matrices for the fp32 multi-CU kernel and for teacher forcing: each bf16 weight (exact in fp32), or each
     // int8 code * scale, rounded to fp32 once here (the per-stream kernel multiplies its row sums by
     // the scale instead)
     size_t ftotal = 0;
@@ -569,13 +630,23 @@ int wn_create(const wn_config* c, const wn_weights* w, wn_handle** out) {
     }
     h->group_ok = true;
   }
+  if (h->force.empty() && 2 * cus >= WN_TEACH_TILES && coop && (size_t)lds_max >= wn_teach_lds_bytes(R, S)) {
+    e = hipMalloc(&h->dteach, wn_teach_packed_floats(L, R, S) * sizeof(float));
+    if (e == hipSuccess) e = wn_teach_pack(L, R, S, h->dmem_f32 ? h->w_chain : h->w, static_cast<float*>(h->dteach), &h->teach);
+    if (e != hipSuccess) {
+      wn_destroy(h);
+      return e == hipErrorOutOfMemory ? fail(WN_ENOMEM, "hipMalloc of teacher forcing's weights")
+                                      : hip_fail(e, "packing teacher forcing's weights");
+    }
+    h->teach_ok = true;
+  }
   *out = h;
   return WN_OK;
 }
 
 size_t wn_workspace_bytes(const wn_handle* h, int32_t B) {
   if (!h || B < 1) return 0;
-  return ws_layout(h, B).total;
+  return ws_layout(h, B).total + teach_bytes(h, B);
 }
 
 int wn_generate(wn_handle* h, int32_t B, int32_t T, const float* cond, const float* uniforms, int32_t* samples,
@@ -583,7 +654,7 @@ int wn_generate(wn_handle* h, int32_t B, int32_t T, const float* cond, const flo
   g_err.clear();
   int rc = check_call(h, B, T, cond, uniforms, samples, workspace, ws_bytes, reset);
   if (rc != WN_OK || T == 0) return rc;
-  return launch(h, B, T, cond, uniforms, nullptr, samples, nullptr, workspace, reset, stream, false, kDirect);
+  return launch(h, B, T, cond, uniforms, nullptr, samples, nullptr, workspace, ws_bytes, reset, stream, false, kDirect);
 }
 
 int wn_generate_sampled(wn_handle* h, int32_t B, int32_t T, const float* cond, const float* uniforms,
@@ -595,7 +666,7 @@ int wn_generate_sampled(wn_handle* h, int32_t B, int32_t T, const float* cond, c
   if (rc != WN_OK) return rc;
   rc = check_call(h, B, T, cond, uniforms, samples, workspace, ws_bytes, reset);
   if (rc != WN_OK || T == 0) return rc;
-  return launch(h, B, T, cond, uniforms, nullptr, samples, nullptr, workspace, reset, stream, false, sp);
+  return launch(h, B, T, cond, uniforms, nullptr, samples, nullptr, workspace, ws_bytes, reset, stream, false, sp);
 }
 
 int wn_teacher_force(wn_handle* h, int32_t B, int32_t T, const float* cond, const int32_t* y, float* logits,
@@ -603,7 +674,7 @@ int wn_teacher_force(wn_handle* h, int32_t B, int32_t T, const float* cond, cons
   g_err.clear();
   int rc = check_call(h, B, T, cond, y, logits, workspace, ws_bytes, reset);
   if (rc != WN_OK || T == 0) return rc;
-  return launch(h, B, T, cond, nullptr, y, nullptr, logits, workspace, reset, stream, true, kDirect);
+  return launch(h, B, T, cond, nullptr, y, nullptr, logits, workspace, ws_bytes, reset, stream, true, kDirect);
 }
 
 int wn_status(wn_handle* h, const void* workspace, void* stream) {
@@ -663,6 +734,7 @@ void wn_destroy(wn_handle* h) {
     if (h->dmem) (void)hipFree(h->dmem);
     if (h->dpack) (void)hipFree(h->dpack);
     if (h->dmem_f32) (void)hipFree(h->dmem_f32);
+    if (h->dteach) (void)hipFree(h->dteach);
     if (h->abort_host) (void)hipHostFree(h->abort_host);
   }
   delete h;

@@ -1,0 +1,129 @@
+"""Teacher forcing of every step at once (the default handle's teacher_force) against the CPU oracle, and
+against the step-by-step kernels, whose histories it continues and leaves.
+
+Each case runs a call from zero at the sizes where the tiling turns: one launch for calls of up to 16
+steps (several streams per 16-row tile), whole passes beyond (a partial last tile, rows of several
+streams in one tile, dilations longer than the call, than a tile and of 1), on every history layout
+(fp32 words, tagged words, bf16 pairs, the MFMA kernel's tiles).  Logits: every product and sum is fp32,
+so their error against the 64-bit oracle is that of fp32 sums of up to l r terms of order 1 (measured
+up to 2e-6; int8 and bf16 models on exact weights alike); the bound is 1e-5.  The batched kernel's histories
+hold two bf16 parts of a value (2^-17 of it, times sums over r = 64 of weights of 1/sqrt(2 r), over
+l layers): 1e-4.
+"""
+import zlib
+
+import numpy as np
+import pytest
+
+import oracle
+import synth
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+CASES = [
+    # name, L, dilations, r, s, B, T, dtype, taps, approx, kernel family of the state
+    ("stream_tiny", 4, (1, 2, 4, 8), 16, 32, 3, 17, "f32", 1, False, "stream_l2"),
+    ("stream_tiny_bf16", 4, (1, 2, 4, 8), 16, 32, 5, 100, "bf16", 2, False, "stream_l2"),
+    ("stream_tiny_i8_t16", 3, (3, 1, 40), 16, 32, 2, 16, "i8", 1, False, "stream_l2"),
+    ("chain_r32", 5, (1, 3, 9, 27, 81), 32, 128, 2, 333, "f32", 1, False, "multi_cu_chain"),
+    ("chain_r64_s128", 6, (1, 2, 4, 8, 16, 64), 64, 128, 1, 65, "f32", 1, True, "multi_cu_chain"),
+    ("chain_l20", 20, tuple(synth.dilation_cycle(20)), 64, 256, 1, 1300, "f32", 2, False, "multi_cu_chain"),
+    ("chain_l20_t15_b3", 20, tuple(synth.dilation_cycle(20)), 64, 256, 3, 15, "f32", 1, False, "multi_cu_chain"),
+    ("chain_r128", 7, (1, 2, 4, 8, 16, 32, 64), 128, 256, 3, 50, "f32", 1, False, "multi_cu_chain"),
+    ("chain_r128_t5_b7", 4, (1, 7, 2, 3), 128, 256, 7, 5, "f32", 2, True, "multi_cu_chain"),
+    ("chain_bf16_b2", 6, (1, 2, 4, 8, 16, 32), 64, 256, 2, 90, "bf16", 1, False, "multi_cu_chain"),
+    ("mfma_b37", 8, (1, 2, 4, 8, 16, 32, 64, 128), 64, 256, 170, 40, "bf16", 1, False, "multi_cu_mfma"),
+    ("mfma_i8_t1", 8, (1, 2, 4, 8, 16, 32, 64, 128), 64, 256, 170, 1, "i8", 2, False, "multi_cu_mfma"),
+    ("group_s128", 5, (1, 2, 4, 8, 16), 64, 128, 150, 25, "bf16", 1, False, "mfma_group"),
+]
+
+
+def _sequence(net, cond, u, y, cuts):
+    """Generation, teacher forcing in the given pieces, then generation, all on one state."""
+    ws = net.new_workspace(cond.shape[0])
+    n = u.shape[1] // 2
+    first = net.generate(cond[:, :n].contiguous(), u[:, :n].contiguous(), workspace=ws)
+    lg, a = [], 0
+    for b in cuts:
+        lg.append(net.teacher_force(cond[:, n + a:n + b].contiguous(), y[:, a:b].contiguous(), workspace=ws, reset=False))
+        a = b
+    last = net.generate(cond[:, n + a:].contiguous(), u[:, n:].contiguous(), workspace=ws, reset=False)
+    assert net.status(ws) == 0
+    return first, torch.cat(lg, 1), last
+
+
+@pytest.mark.parametrize("case", CASES, ids=[c[0] for c in CASES])
+def test_teacher_forcing_parallel(case, monkeypatch):
+    import paper_1702_07825_amd as wn
+    name, L, dil, r, s, B, T, dtype, taps, approx, family = case
+    print("teacher forcing %s: L=%d r=%d s=%d B=%d T=%d %s" % (name, L, r, s, B, T, dtype), flush=True)
+    seed = zlib.crc32(name.encode()) % 1000
+    w = synth.make_weights(L, r, s, seed=seed, bias_scale=0.2, embed_taps=taps)
+    net = wn.WaveNet(w, dil, weight_dtype=dtype, approx_nonlin=approx)
+    assert net.kernel_variant(B) == family
+    monkeypatch.setenv("WN_KERNEL", "stream" if family == "stream_l2" else family)
+    step = wn.WaveNet(w, dil, weight_dtype=dtype, approx_nonlin=approx)  # step by step
+    monkeypatch.delenv("WN_KERNEL")
+    assert step.kernel_variant(B) == family
+    bound = 1e-4 if family in ("mfma_group", "multi_cu_mfma") else 1e-5
+    cond = synth.make_cond(L, r, B, T + 10, seed=seed, device="cuda")
+    u = torch.tensor(synth.make_uniforms(B, 10, seed=seed), device="cuda")
+    y = torch.tensor(synth.make_samples(B, T, seed=seed), device="cuda")
+
+    lg = net.teacher_force(cond[:, :T].contiguous(), y)
+    mode = {"bf16": {"bf16_weights": True}, "i8": {"int8_weights": True}}.get(dtype, {})
+    model = oracle.Model(w, dil, approx_nonlin=approx, **mode)
+    some = sorted({0, B // 2, B - 1})
+    _, lo, _ = oracle.run_streams(model, cond[some, :T].cpu().numpy(), y_in=y[some].cpu().numpy(), threads=3)
+    err = float(np.abs(lg[some].cpu().numpy() - lo).max())
+    print("  max|dlogit| oracle %.3g" % err, flush=True)
+    assert err <= (1e-4 if family == "mfma_group" else 1e-5)
+
+    # on a state that generation left, in one call and cut where the two forms meet: the same logits
+    # bit for bit, within the step kernels' own error of theirs, and a state they continue alike
+    f0, l0, g0 = _sequence(net, cond, u, y, (T,))
+    f1, l1, g1 = _sequence(net, cond, u, y, tuple(sorted({1, min(T, 16), min(T, 17), T})))
+    f2, l2, g2 = _sequence(step, cond, u, y, (T,))
+    assert torch.equal(f0, f1) and torch.equal(f0, f2)
+    assert torch.equal(l0, l1) and torch.equal(g0, g1)
+    assert float((l0 - l2).abs().max()) <= 2 * bound
+    # draws part where a uniform lies within that error of a CDF value: at most a few streams of a batch
+    assert float((g0 != g2).any(1).float().mean()) <= (0.0 if B < 8 else 0.05)
+
+    # a workspace without the scratch serves the call step by step
+    ws = net.new_workspace(B)
+    small = ws[:step.workspace_bytes(B)]
+    assert torch.equal(net.teacher_force(cond[:, :T].contiguous(), y, workspace=small),
+                       step.teacher_force(cond[:, :T].contiguous(), y))
+
+    # a standing abort request: nothing is written
+    net.abort(True)
+    out = torch.full((B, T, 256), -1.0, device="cuda")
+    net.teacher_force(cond[:, :T].contiguous(), y, logits=out, workspace=ws)
+    assert net.status(ws) == wn.WN_EABORTED and bool((out == -1.0).all())
+    net.abort(False)
+    assert torch.equal(net.teacher_force(cond[:, :T].contiguous(), y, workspace=ws), lg) and net.status(ws) == 0
+    net.close()
+    step.close()
+
+
+def test_chunks_of_a_long_call():
+    """More rows than the scratch holds: chunks over steps and over streams give the same logits as calls
+    that fit (4 layers, so that the sizes stay small)."""
+    import paper_1702_07825_amd as wn
+    w = synth.make_weights(4, 16, 32, seed=3, bias_scale=0.2)
+    net = wn.WaveNet(w, (1, 5, 300, 2))
+    for B, T in ((1, 40000), (200, 403)):
+        print("chunks: B=%d T=%d" % (B, T), flush=True)
+        cond = synth.make_cond(4, 16, B, T, seed=4, device="cuda")
+        y = torch.tensor(synth.make_samples(B, T, seed=4), device="cuda")
+        whole = net.teacher_force(cond, y)
+        parts = [net.teacher_force(cond[b:b + 1, :1500].contiguous(), y[b:b + 1, :1500].contiguous()) for b in (0, B - 1)]
+        assert torch.equal(whole[0, :1500], parts[0][0]) and torch.equal(whole[B - 1, :1500], parts[1][0])
+        ws = net.new_workspace(B)
+        h = T // 2 + 1
+        a = net.teacher_force(cond[:, :h].contiguous(), y[:, :h].contiguous(), workspace=ws)
+        b = net.teacher_force(cond[:, h:].contiguous(), y[:, h:].contiguous(), workspace=ws, reset=False)
+        assert torch.equal(torch.cat([a, b], 1), whole)
+    net.close()
