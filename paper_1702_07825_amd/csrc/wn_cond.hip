@@ -5,16 +5,16 @@
 //
 // Each layer is two kernels.  The gate pre-activations of all frames at once are a dense
 // contraction, [3h x 2 cin] . [2 cin x B*Tf] per direction (the width-2 convolution: tap 0 is the
-// direction's previous frame, tap 1 the current one), run on fp32 MFMA (v_mfma_f32_16x16x4f32) in
-// 128 x 128 tiles staged through double-buffered LDS; the weights are stored with each tap padded
-// to a multiple of 32 inputs so that K chunks never straddle the taps.  The fo-pool is a linear
-// recurrence along the frames, independent per (stream, direction, channel): one thread each,
-// with the gate pre-activations of 16 frames loaded ahead of the dependent chain.  The second
-// layer's pool writes its output interleaved, and a last kernel repeats every frame over its
-// audio steps with coalesced float4 stores (bound by the HBM write of [B][T][2 h2]).
+// direction's previous frame, tap 1 the current one), run as split bf16 products that keep fp32's
+// precision, in tiles staged through LDS; the weights are stored split, with each tap padded to a
+// multiple of 32 inputs so that K chunks never straddle the taps.  The fo-pool is a linear recurrence
+// along the frames, independent per (stream, direction, channel), run in segments of frames.  The second
+// layer's pool writes its output interleaved, and a last kernel repeats every frame over its audio steps
+// (bound by the HBM write of [B][T][2 h2]).
 #include "wn_cond.h"
 #include "wn.h"
 #include "wn_internal.h"
+#include "wn_mfma.h"
 #include "wn_wave.h"
 
 #include <algorithm>
@@ -27,7 +27,8 @@ struct wn_cond {
   int F = 0, h1 = 0, h2 = 0, fr = 1, ar = 1;
   int cinp1 = 0, cinp2 = 0;  // per-tap input widths of the two layers rounded up to 32
   void* dmem = nullptr;
-  const float *w1 = nullptr, *b1 = nullptr, *w2 = nullptr, *b2 = nullptr;
+  const unsigned short *w1 = nullptr, *w2 = nullptr;  // split (see split3)
+  const float *b1 = nullptr, *b2 = nullptr;
   void* scratch = nullptr;  // device address of this device's copy of `scratch` (wn_condition_static)
 };
 
@@ -38,49 +39,80 @@ static __device__ __align__(256) unsigned char scratch[WN_COND_SCRATCH_BYTES];
 
 namespace {
 
-typedef float f32x4 __attribute__((ext_vector_type(4)));
+using wnk::bf16x8;
+using wnk::f32x4;
+using wnk::u16;
+using wnk::u32x4;
 
 struct GateArgs {
   const float* x;  // [B][Tf][cin]
-  const float* w;  // [2][N][2 cinp]: tap 0 (previous frame) inputs 0..cin-1, tap 1 at cinp.., zeros past cin
+  const u16* w;    // [2][N][2 cinp / 32][3][32]: split weights; tap 0 (previous frame) inputs 0..cin-1, tap 1 at cinp.., zeros past cin
   const float* b;  // [2][N]
   float* p;        // [B][Tf][2][N]
   int B, Tf, cin, cinp, N;
 };
 
+// fp32 products on bf16 MFMA.  A value is split into three bf16 parts, each the nearest to what the ones
+// before leave, v = h + m + l to 2^-25 of it, and a product takes the six of the nine part products that
+// reach fp32's precision (the others are below 2^-26 of it), smallest first, summed in fp32.  Infinities
+// stay in h alone.
+__device__ __forceinline__ void split3(f32x4 v, uint2& h, uint2& m, uint2& l) {
+  h = make_uint2(wnk::pack_bf16(v[0], v[1]), wnk::pack_bf16(v[2], v[3]));
+  const float hv[4] = {wnk::low_bf16(h.x), wnk::high_bf16(h.x), wnk::low_bf16(h.y), wnk::high_bf16(h.y)};
+  float r[4];
+#pragma unroll
+  for (int e = 0; e < 4; ++e) r[e] = hv[e] == v[e] ? 0.f : v[e] - hv[e];
+  m = make_uint2(wnk::pack_bf16(r[0], r[1]), wnk::pack_bf16(r[2], r[3]));
+  l = make_uint2(wnk::pack_bf16(r[0] - wnk::low_bf16(m.x), r[1] - wnk::high_bf16(m.x)),
+                 wnk::pack_bf16(r[2] - wnk::low_bf16(m.y), r[3] - wnk::high_bf16(m.y)));
+}
+
+// Weights [rows][K] (K a multiple of 32) to [rows][K / 32][3][32].
+__global__ __launch_bounds__(256) void split_weights(const float* src, u16* dst, size_t n) {
+  const size_t i = 4 * ((size_t)blockIdx.x * 256 + threadIdx.x);
+  if (i >= n) return;
+  uint2 h, m, l;
+  split3(*reinterpret_cast<const f32x4*>(src + i), h, m, l);
+  u16* d = dst + i / 32 * 96 + i % 32;
+  *reinterpret_cast<uint2*>(d) = h;
+  *reinterpret_cast<uint2*>(d + 32) = m;
+  *reinterpret_cast<uint2*>(d + 64) = l;
+}
+
 // Gate pre-activations of every frame of a layer, both directions (grid.z):
 //   p[b][t][dir][n] = b[dir][n] + sum_k w[dir][n][0][k] x[b][t'][k] + w[dir][n][1][k] x[b][t][k]
 // with t' = t - 1 (forward) or t + 1 (backward) and x = 0 outside the frames: the width-2
-// convolution as one dense contraction [N x 2 cinp] . [2 cinp x B Tf] on fp32 MFMA
-// (v_mfma_f32_16x16x4f32).  128 x 128 output tiles (gate rows x frames) per 256 threads, each wave
-// a 64 x 64 quarter; K in chunks of 32 that never straddle the two taps (cinp is a multiple of
-// 32).  LDS is double-buffered, one barrier per chunk, with the next chunk's global loads in
-// flight during the current chunk's products.  The MFMA A operand is the weight rows and B the
-// frames, so each lane ends with four consecutive gate rows of one frame.  Within a chunk the k
-// index is permuted (lane group q of MFMA step e takes k = 4q + e of each 16), identically for
-// both operands, so one b128 LDS read feeds four MFMA steps.  VX: the input rows are float4
-// aligned (cin % 4 == 0), else they are read one float at a time.
+// convolution as one dense contraction [N x 2 cinp] . [2 cinp x B Tf], in split bf16 products
+// (v_mfma_f32_16x16x32_bf16).  VT x VT output tiles (gate rows x frames) per 256 threads, each wave a
+// quarter; K in chunks of 32 that never straddle the two taps (cinp is a multiple of 32), staged in LDS as
+// the three parts of a row's chunk, with the next chunk's global loads in flight during the current
+// chunk's products and a second block on the CU beside them.  The MFMA A operand is the weight rows and B
+// the frames, so each lane ends with four consecutive gate rows of one frame.  VX: the input rows are
+// float4 aligned (cin % 4 == 0), else they are read one float at a time.
+// Bound: the bf16 matrix rate, six products for one.  Measured, 32 streams x 512 frames: second layer (281
+// GFLOP) 2244 us on fp32 MFMA, 1359 so (207 TFLOP/s, 1.24 PFLOP/s of bf16 products, about what a large
+// bf16 matrix product reaches on the card); error against 64 bits 3.4e-7 and 3.2e-7 (of the whole network).
 constexpr int NTG = 256;
-constexpr int VM = 128, VN = 128, VK = 32, VLD = VK + 8;  // tile, K chunk, LDS row (floats)
+constexpr int VK = 32, VLD = 3 * VK + 16;  // K chunk; LDS row (16-bit units): 32 bytes mod 64, free of bank conflicts
 
-template <bool VX>
+template <int VT, bool VX>
 __global__ __launch_bounds__(NTG, 2) void qrnn_gate_gemm(const GateArgs a) {
+  constexpr int NI = VT / 32, ND = VT / 32;  // rows per thread of a chunk of x; 16 x 16 tiles per wave side
+  constexpr int NW = VT * 12 / NTG;          // 16-byte pieces of a chunk of weights per thread
   const int dir = blockIdx.z;
-  const int m0 = blockIdx.x * VM, n0 = blockIdx.y * VN;
+  const int m0 = blockIdx.x * VT, n0 = blockIdx.y * VT;
   const int M = a.B * a.Tf, K = 2 * a.cinp, N = a.N;
-  __shared__ __align__(16) float Ws[2][VN][VLD];
-  __shared__ __align__(16) float Xs[2][VM][VLD];
+  __shared__ __align__(16) u16 Ws[VT][VLD];
+  __shared__ __align__(16) u16 Xs[VT][VLD];
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-  const int wn = (wave >> 1) * 64, wm = (wave & 1) * 64;
+  const int wn = (wave >> 1) * (VT / 2), wm = (wave & 1) * (VT / 2);
   const int r16 = lane & 15, q = lane >> 4;
-  // global -> LDS assignment: rows tid/8 + 32 i, float4 column tid % 8 of the chunk
+  // x: rows tid / 8 + 32 i, float4 column tid % 8 of the chunk
   const int lr = tid >> 3, lc = (tid & 7) * 4;
-  const float* wd = a.w + (size_t)dir * N * K;
-  const float* xcur[4];
-  const float* xprev[4];
-  const float* wrow[4];
+  const float* xcur[NI];
+  const float* xprev[NI];
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
+  for (int i = 0; i < NI; ++i) {
     const int m = m0 + lr + 32 * i;
     xcur[i] = xprev[i] = nullptr;
     if (m < M) {
@@ -89,15 +121,24 @@ __global__ __launch_bounds__(NTG, 2) void qrnn_gate_gemm(const GateArgs a) {
       xcur[i] = a.x + ((size_t)bb * a.Tf + t) * a.cin;
       if (tp >= 0 && tp < a.Tf) xprev[i] = a.x + ((size_t)bb * a.Tf + tp) * a.cin;
     }
-    const int n = n0 + lr + 32 * i;
-    wrow[i] = n < N ? wd + (size_t)n * K + lc : nullptr;
   }
-  f32x4 gx[4], gw[4];
-  auto load = [&](int k0) {
+  // weights: piece tid + 256 i is piece (.. % 12) of row (.. / 12); rows past N repeat the last one
+  const u32x4* wsrc[NW];
+  int wdst[NW];
+#pragma unroll
+  for (int i = 0; i < NW; ++i) {
+    const int pc = tid + NTG * i, row = pc / 12, c = pc % 12;
+    wsrc[i] = reinterpret_cast<const u32x4*>(a.w + ((size_t)dir * N + min(n0 + row, N - 1)) * K * 3) + c;
+    wdst[i] = row * VLD + c * 8;
+  }
+  f32x4 gx[NI];
+  u32x4 gw[NW];
+  auto load = [&](int c) {
+    const int k0 = c * VK;
     const bool prev = k0 < a.cinp;
     const int kk = (prev ? k0 : k0 - a.cinp) + lc;  // input index of this thread's first float
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
+    for (int i = 0; i < NI; ++i) {
       const float* xp = prev ? xprev[i] : xcur[i];
       if (VX) {
         gx[i] = xp && kk < a.cin ? *reinterpret_cast<const f32x4*>(xp + kk) : f32x4{0.f, 0.f, 0.f, 0.f};
@@ -105,50 +146,56 @@ __global__ __launch_bounds__(NTG, 2) void qrnn_gate_gemm(const GateArgs a) {
 #pragma unroll
         for (int e = 0; e < 4; ++e) gx[i][e] = xp && kk + e < a.cin ? xp[kk + e] : 0.f;
       }
-      gw[i] = wrow[i] ? *reinterpret_cast<const f32x4*>(wrow[i] + k0) : f32x4{0.f, 0.f, 0.f, 0.f};
     }
-  };
-  auto stash = [&](int buf) {
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      *reinterpret_cast<f32x4*>(&Xs[buf][lr + 32 * i][lc]) = gx[i];
-      *reinterpret_cast<f32x4*>(&Ws[buf][lr + 32 * i][lc]) = gw[i];
+    for (int i = 0; i < NW; ++i) gw[i] = wsrc[i][12 * c];
+  };
+  auto stash = [&] {
+#pragma unroll
+    for (int i = 0; i < NI; ++i) {
+      uint2 h, m, l;
+      split3(gx[i], h, m, l);
+      u16* d = &Xs[lr + 32 * i][lc];
+      *reinterpret_cast<uint2*>(d) = h;
+      *reinterpret_cast<uint2*>(d + 32) = m;
+      *reinterpret_cast<uint2*>(d + 64) = l;
     }
+#pragma unroll
+    for (int i = 0; i < NW; ++i) *reinterpret_cast<u32x4*>(&Ws[0][0] + wdst[i]) = gw[i];
   };
-  f32x4 acc[4][4];
+  f32x4 acc[ND][ND];
 #pragma unroll
-  for (int i = 0; i < 4; ++i)
+  for (int i = 0; i < ND; ++i)
 #pragma unroll
-    for (int j = 0; j < 4; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int j = 0; j < ND; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
   load(0);
-  stash(0);
-  __syncthreads();
   const int nk = K / VK;
   for (int c = 0; c < nk; ++c) {
-    const int buf = c & 1;
-    if (c + 1 < nk) load((c + 1) * VK);
+    stash();
+    wnk::lds_barrier();
+    load(min(c + 1, nk - 1));
+    bf16x8 wa[ND][3], xb[ND][3];
 #pragma unroll
-    for (int h = 0; h < VK; h += 16) {
-      f32x4 wa[4], xb[4];
+    for (int i = 0; i < ND; ++i)
 #pragma unroll
-      for (int i = 0; i < 4; ++i) wa[i] = *reinterpret_cast<const f32x4*>(&Ws[buf][wn + 16 * i + r16][h + 4 * q]);
+      for (int s = 0; s < 3; ++s) {
+        wa[i][s] = *reinterpret_cast<const bf16x8*>(&Ws[wn + 16 * i + r16][32 * s + 8 * q]);
+        xb[i][s] = *reinterpret_cast<const bf16x8*>(&Xs[wm + 16 * i + r16][32 * s + 8 * q]);
+      }
+    constexpr int PA[6] = {0, 2, 1, 0, 1, 0}, PB[6] = {2, 0, 1, 1, 0, 0};
 #pragma unroll
-      for (int j = 0; j < 4; ++j) xb[j] = *reinterpret_cast<const f32x4*>(&Xs[buf][wm + 16 * j + r16][h + 4 * q]);
+    for (int s = 0; s < 6; ++s)
 #pragma unroll
-      for (int e = 0; e < 4; ++e)
+      for (int i = 0; i < ND; ++i)
 #pragma unroll
-        for (int i = 0; i < 4; ++i)
-#pragma unroll
-          for (int j = 0; j < 4; ++j)
-            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(wa[i][e], xb[j][e], acc[i][j], 0, 0, 0);
-    }
-    if (c + 1 < nk) stash(buf ^ 1);
-    __syncthreads();
+        for (int j = 0; j < ND; ++j)
+          acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wa[i][PA[s]], xb[j][PB[s]], acc[i][j], 0, 0, 0);
+    wnk::lds_barrier();
   }
   // acc[i][j]: lane holds gate rows wn + 16 i + 4 q .. +3 of frame wm + 16 j + r16
   const float* bd = a.b + (size_t)dir * N;
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
+  for (int i = 0; i < ND; ++i) {
     const int n = n0 + wn + 16 * i + 4 * q;
     if (n >= N) continue;
     const bool whole = (N & 3) == 0;  // then n + 3 < N and the row offsets are float4 aligned
@@ -156,7 +203,7 @@ __global__ __launch_bounds__(NTG, 2) void qrnn_gate_gemm(const GateArgs a) {
 #pragma unroll
     for (int v = 0; v < 4; ++v) bias[v] = n + v < N ? bd[n + v] : 0.f;
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
+    for (int j = 0; j < ND; ++j) {
       const int m = m0 + wm + 16 * j + r16;
       if (m >= M) continue;
       float* dst = a.p + ((size_t)m * 2 + dir) * N + n;
@@ -310,14 +357,21 @@ class DeviceScope {
   bool ok_ = false;
 };
 
-hipError_t run_layer(const float* x, int B, int Tf, int cin, int cinp, int H, const float* w, const float* b,
+hipError_t run_layer(const float* x, int B, int Tf, int cin, int cinp, int H, const u16* w, const float* b,
                      float* p, float* out, int interleave, hipStream_t st) {
   GateArgs g{x, w, b, p, B, Tf, cin, cinp, 3 * H};
-  const dim3 grid((unsigned)((B * Tf + VM - 1) / VM), (unsigned)((3 * H + VN - 1) / VN), 2);
-  if (cin % 4 == 0 && reinterpret_cast<uintptr_t>(x) % 16 == 0)
-    hipLaunchKernelGGL(qrnn_gate_gemm<true>, grid, dim3(NTG), 0, st, g);
-  else
-    hipLaunchKernelGGL(qrnn_gate_gemm<false>, grid, dim3(NTG), 0, st, g);
+  const bool vx = cin % 4 == 0 && reinterpret_cast<uintptr_t>(x) % 16 == 0;
+  // 128 x 128 tiles where they fill the chip twice (two blocks share a CU), else 64 x 64: one
+  // stream of 256 frames, second layer, 120 blocks of 128 x 128 on fp32 MFMA 85 us, 480 of 64 x 64 41 us.
+  auto blocks = [&](int t) { return dim3((unsigned)((B * Tf + t - 1) / t), (unsigned)((3 * H + t - 1) / t), 2); };
+  const dim3 big = blocks(128), small = blocks(64);
+  if ((size_t)big.x * big.y * 2 >= 512) {
+    if (vx) hipLaunchKernelGGL((qrnn_gate_gemm<128, true>), big, dim3(NTG), 0, st, g);
+    else hipLaunchKernelGGL((qrnn_gate_gemm<128, false>), big, dim3(NTG), 0, st, g);
+  } else {
+    if (vx) hipLaunchKernelGGL((qrnn_gate_gemm<64, true>), small, dim3(NTG), 0, st, g);
+    else hipLaunchKernelGGL((qrnn_gate_gemm<64, false>), small, dim3(NTG), 0, st, g);
+  }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   PoolArgs pa{p, out, B, Tf, H, interleave};
@@ -433,8 +487,10 @@ int wn_cond_create(const wn_cond_config* cfg, const wn_cond_weights* w, wn_cond*
     return wn_set_last_error(WN_ENOMEM, "host allocation");
   }
   const size_t n_b1 = (size_t)2 * 3 * c->h1, n_b2 = (size_t)2 * 3 * c->h2;
-  const size_t o_b1 = align_up(w1p.size() * 4, 256), o_w2 = align_up(o_b1 + n_b1 * 4, 256);
-  const size_t o_b2 = align_up(o_w2 + w2p.size() * 4, 256), total = align_up(o_b2 + n_b2 * 4, 256);
+  // split weights, biases, and the fp32 weights of one layer at a time while they are split
+  const size_t o_w2 = align_up(w1p.size() * 6, 256), o_b1 = align_up(o_w2 + w2p.size() * 6, 256);
+  const size_t o_b2 = align_up(o_b1 + n_b1 * 4, 256), o_f = align_up(o_b2 + n_b2 * 4, 256);
+  const size_t total = align_up(o_f + std::max(w1p.size(), w2p.size()) * 4, 256);
   hipError_t e = hipMalloc(&c->dmem, total);
   if (e != hipSuccess) {
     delete c;
@@ -442,19 +498,29 @@ int wn_cond_create(const wn_cond_config* cfg, const wn_cond_weights* w, wn_cond*
                                     : wn_set_last_error(WN_EHIP, hipGetErrorString(e));
   }
   char* d = static_cast<char*>(c->dmem);
-  const struct { const float* src; size_t n, off; } parts[] = {
-      {w1p.data(), w1p.size(), 0}, {w->b1, n_b1, o_b1}, {w2p.data(), w2p.size(), o_w2}, {w->b2, n_b2, o_b2}};
-  for (const auto& pt : parts) {
-    if (e == hipSuccess) e = hipMemcpy(d + pt.off, pt.src, pt.n * 4, hipMemcpyHostToDevice);
-  }
+  auto upload = [&](size_t off, const float* src, size_t n) {
+    if (e == hipSuccess) e = hipMemcpy(d + off, src, n * 4, hipMemcpyHostToDevice);
+  };
+  auto split = [&](size_t off, const std::vector<float>& w) {
+    upload(o_f, w.data(), w.size());
+    if (e != hipSuccess) return;
+    hipLaunchKernelGGL(split_weights, dim3((unsigned)((w.size() / 4 + 255) / 256)), dim3(256), 0, nullptr,
+                       reinterpret_cast<const float*>(d + o_f), reinterpret_cast<u16*>(d + off), w.size());
+    e = hipGetLastError();
+    if (e == hipSuccess) e = hipStreamSynchronize(nullptr);
+  };
+  split(0, w1p);
+  split(o_w2, w2p);
+  upload(o_b1, w->b1, n_b1);
+  upload(o_b2, w->b2, n_b2);
   if (e != hipSuccess) {
     (void)hipFree(c->dmem);
     delete c;
     return wn_set_last_error(WN_EHIP, hipGetErrorString(e));
   }
-  c->w1 = reinterpret_cast<const float*>(d);
+  c->w1 = reinterpret_cast<const u16*>(d);
+  c->w2 = reinterpret_cast<const u16*>(d + o_w2);
   c->b1 = reinterpret_cast<const float*>(d + o_b1);
-  c->w2 = reinterpret_cast<const float*>(d + o_w2);
   c->b2 = reinterpret_cast<const float*>(d + o_b2);
   *out = c;
   return WN_OK;

@@ -1,0 +1,44 @@
+"""The conditioning network at the sizes where its kernels turn: the contraction's 128 x 128 tiles (from 512
+blocks on, ragged in frames and gate rows) beside the 64 x 64 ones, the pool's passes of 128 frames in
+segments of 16 (one frame more and less), and an output whose rows end inside a block's run of 1024 pieces.
+
+Against the oracle (64-bit): the split bf16 products keep fp32's precision, so a gate pre-activation of up to
+1024 terms with standard deviation near 1 is off by about 1024^(1/2) x 2^-24 = 2e-6, and the outputs, bounded by
+1, by a few times that (measured up to 4e-6 of their rms): 2e-5.  Features of 2^60 put the parts of a value far apart and
+saturate the gates, which hold to the same bound."""
+import numpy as np
+import pytest
+
+import oracle
+import synth
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+CASES = [
+    # name, F, h1, n_layers, r, B, n_frames, frame_rate, audio_rate, scale of the features
+    ("tiles128", 227, 256, 20, 64, 5, 221, 256, 300, 1.0),
+    ("seg127", 36, 40, 2, 19, 3, 127, 3, 8, 1.0),
+    ("seg128", 36, 40, 2, 19, 2, 128, 3, 8, 1.0),
+    ("seg129", 36, 40, 2, 19, 2, 129, 3, 8, 1.0),
+    ("seg257_wide", 64, 32, 2, 32, 1, 257, 256, 16000, 1.0),
+    ("saturated", 227, 48, 2, 16, 2, 40, 1, 1, 2.0 ** 60),
+]
+
+
+@pytest.mark.parametrize("case", CASES, ids=[c[0] for c in CASES])
+def test_conditioning_tiles(case):
+    import paper_1702_07825_amd as wn
+    name, F, h1, L, r, B, Tf, fr, ar, scale = case
+    print("cond tiles %s" % name, flush=True)
+    w = synth.make_cond_weights(F, h1, L * r, seed=len(name), bias_scale=0.2)
+    x = (np.random.default_rng(7).normal(0, 1, (B, Tf, F)) * scale).astype(np.float32)
+    T = (Tf * ar) // fr
+    net = wn.Conditioner(w, L, r, fr, ar)
+    got = net(torch.tensor(x, device="cuda"), T).cpu().numpy().reshape(B, T, 2 * L * r)
+    for b in sorted({0, B - 1}):
+        ref = oracle.condition(w, x[b], T, fr, ar)
+        err = float(np.abs(got[b] - ref).max())
+        print("  stream %d max|dcond| = %.3g" % (b, err), flush=True)
+        assert err <= 2e-5
+    net.close()
