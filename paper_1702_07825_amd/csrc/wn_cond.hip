@@ -487,10 +487,10 @@ int wn_cond_create(const wn_cond_config* cfg, const wn_cond_weights* w, wn_cond*
     return wn_set_last_error(WN_ENOMEM, "host allocation");
   }
   const size_t n_b1 = (size_t)2 * 3 * c->h1, n_b2 = (size_t)2 * 3 * c->h2;
-  // split weights, biases, and the fp32 weights of one layer at a time while they are split
+  // split weights, biases, and the fp32 weights they are split from
   const size_t o_w2 = align_up(w1p.size() * 6, 256), o_b1 = align_up(o_w2 + w2p.size() * 6, 256);
   const size_t o_b2 = align_up(o_b1 + n_b1 * 4, 256), o_f = align_up(o_b2 + n_b2 * 4, 256);
-  const size_t total = align_up(o_f + std::max(w1p.size(), w2p.size()) * 4, 256);
+  const size_t total = align_up(o_f + (w1p.size() + w2p.size()) * 4, 256);
   hipError_t e = hipMalloc(&c->dmem, total);
   if (e != hipSuccess) {
     delete c;
@@ -501,18 +501,18 @@ int wn_cond_create(const wn_cond_config* cfg, const wn_cond_weights* w, wn_cond*
   auto upload = [&](size_t off, const float* src, size_t n) {
     if (e == hipSuccess) e = hipMemcpy(d + off, src, n * 4, hipMemcpyHostToDevice);
   };
-  auto split = [&](size_t off, const std::vector<float>& w) {
-    upload(o_f, w.data(), w.size());
+  auto split = [&](size_t off, size_t from, const std::vector<float>& w) {
+    upload(from, w.data(), w.size());
     if (e != hipSuccess) return;
     hipLaunchKernelGGL(split_weights, dim3((unsigned)((w.size() / 4 + 255) / 256)), dim3(256), 0, nullptr,
-                       reinterpret_cast<const float*>(d + o_f), reinterpret_cast<u16*>(d + off), w.size());
+                       reinterpret_cast<const float*>(d + from), reinterpret_cast<u16*>(d + off), w.size());
     e = hipGetLastError();
-    if (e == hipSuccess) e = hipStreamSynchronize(nullptr);
   };
-  split(0, w1p);
-  split(o_w2, w2p);
+  split(0, o_f, w1p);
+  split(o_w2, o_f + w1p.size() * 4, w2p);
   upload(o_b1, w->b1, n_b1);
   upload(o_b2, w->b2, n_b2);
+  if (e == hipSuccess) e = hipStreamSynchronize(nullptr);
   if (e != hipSuccess) {
     (void)hipFree(c->dmem);
     delete c;

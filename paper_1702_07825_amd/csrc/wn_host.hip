@@ -27,8 +27,7 @@ struct wn_handle {
   bool chain_ok = false;  // the multi-CU kernel can serve this model (fp32, supported shape)
   bool xcd_map = false;   // blocks of the multi-CU kernel's grid run on XCD (block mod 8)
   bool teach_ok = false;  // teacher forcing takes all steps of a call at once (wn_teach.hip)
-  void* dteach = nullptr;  // its packed fp32 weights
-  WnTeachWeights teach{};
+  WnTeachWeights teach{};  // its packed fp32 weights, behind the fp32 matrices (dmem or dmem_f32)
   bool group_ok = false;  // the batched MFMA kernel serves every B
   bool mchain_ok = false; // the multi-CU MFMA kernel can serve this model (bf16 or int8, supported shape)
   // WN_KERNEL at wn_create: the one kernel family calls may use ("" = the default choice); a call the
@@ -492,6 +491,15 @@ int wn_create(const wn_config* c, const wn_weights* w, wn_handle** out) {
       total = align_up(total + a.n / a.cols * 4, 256);
     }
   }
+  // The multi-CU kernels and teacher forcing need one CU per block (or two blocks) of their grids.
+  if (const char* force = std::getenv("WN_KERNEL")) h->force = force;
+  int cus = 0, coop = 0, lds_max = 0;
+  (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, h->device);
+  (void)hipDeviceGetAttribute(&coop, hipDeviceAttributeCooperativeLaunch, h->device);
+  (void)hipDeviceGetAttribute(&lds_max, hipDeviceAttributeMaxSharedMemoryPerBlock, h->device);
+  const bool teach = h->force.empty() && 2 * cus >= WN_TEACH_TILES && coop && (size_t)lds_max >= wn_teach_lds_bytes(R, S);
+  const size_t teach_floats = teach ? wn_teach_packed_floats(L, R, S) : 0;
+  float* teach_at = nullptr;
   std::vector<unsigned char> host(total, 0);
   for (const Arr& a : arrs) {
     if (a.matrix && bf) {
@@ -504,7 +512,7 @@ int wn_create(const wn_config* c, const wn_weights* w, wn_handle** out) {
       std::memcpy(host.data() + a.off, a.src, a.n * 4);
     }
   }
-  hipError_t e = hipMalloc(&h->dmem, total);
+  hipError_t e = hipMalloc(&h->dmem, total + (h->dtype == WN_F32 ? teach_floats * 4 : 0));
   if (e != hipSuccess) {
     delete h;
     return e == hipErrorOutOfMemory ? fail(WN_ENOMEM, "hipMalloc of weights") : hip_fail(e, "hipMalloc");
@@ -562,11 +570,7 @@ int wn_create(const wn_config* c, const wn_weights* w, wn_handle** out) {
   // The multi-CU kernels need one CU per block of their grid and a supported shape: the fp32 one runs
   // on fp32 weights (for bf16 and int8 models on an exact fp32 copy), the MFMA one on bf16 or int8
   // weights.
-  if (const char* force = std::getenv("WN_KERNEL")) h->force = force;
   const bool want_chain = h->force != "stream";
-  int cus = 0, coop = 0;
-  (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, h->device);
-  (void)hipDeviceGetAttribute(&coop, hipDeviceAttributeCooperativeLaunch, h->device);
   if (want_chain && wn_chain_supported(R, S, L) && cus >= WN_CHAIN_GRID && coop) h->chain_ok = true;
   if (want_chain && (bf || i8) && wn_mchain_supported(R, S, L) && cus >= WN_CHAIN_GRID && coop) h->mchain_ok = true;
   if (h->chain_ok || h->mchain_ok) h->xcd_map = wn_chain_xcd_map_ok();
@@ -594,7 +598,7 @@ int wn_create(const wn_config* c, const wn_weights* w, wn_handle** out) {
         for (size_t i = 0; i < arrs[k].n; ++i) fh[foff[k] / 4 + i] = (float)codes[i] * scale[i / arrs[k].cols];
       }
     }
-    e = hipMalloc(&h->dmem_f32, ftotal);
+    e = hipMalloc(&h->dmem_f32, ftotal + teach_floats * 4);
     if (e == hipSuccess) e = hipMemcpy(h->dmem_f32, fh.data(), ftotal, hipMemcpyHostToDevice);
     if (e != hipSuccess) {
       if (h->dmem_f32) (void)hipFree(h->dmem_f32);
@@ -604,6 +608,7 @@ int wn_create(const wn_config* c, const wn_weights* w, wn_handle** out) {
       return e == hipErrorOutOfMemory ? fail(WN_ENOMEM, "hipMalloc of fp32 weights") : hip_fail(e, "fp32 weights upload");
     }
     char* f = static_cast<char*>(h->dmem_f32);
+    teach_at = reinterpret_cast<float*>(f + ftotal);
     h->w_chain = h->w;
     h->w_chain.embed = f + foff[0] + (size_t)(c->embed_taps - 1) * A * R * 4;
     h->w_chain.embed_prev = c->embed_taps == 2 ? f + foff[0] : nullptr;
@@ -617,8 +622,6 @@ int wn_create(const wn_config* c, const wn_weights* w, wn_handle** out) {
     h->w_chain.bf16 = 0;
   }
   // The batched MFMA kernel needs bf16 weights, r = 64 and its LDS footprint on one CU.
-  int lds_max = 0;
-  (void)hipDeviceGetAttribute(&lds_max, hipDeviceAttributeMaxSharedMemoryPerBlock, h->device);
   if (want_chain && bf && wn_group_supported(R, S, L) && wn_group_lds_bytes(L, S, c->embed_taps == 2) + 256 <= (size_t)lds_max) {
     const std::vector<uint16_t> tiles =
         wn_group_pack(L, R, S, w->w_prev, w->w_cur, w->w_res, w->w_skip, w->w_relu, w->w_out);
@@ -634,13 +637,12 @@ int wn_create(const wn_config* c, const wn_weights* w, wn_handle** out) {
     }
     h->group_ok = true;
   }
-  if (h->force.empty() && 2 * cus >= WN_TEACH_TILES && coop && (size_t)lds_max >= wn_teach_lds_bytes(R, S)) {
-    e = hipMalloc(&h->dteach, wn_teach_packed_floats(L, R, S) * sizeof(float));
-    if (e == hipSuccess) e = wn_teach_pack(L, R, S, h->dmem_f32 ? h->w_chain : h->w, static_cast<float*>(h->dteach), &h->teach);
+  if (teach) {
+    if (h->dtype == WN_F32) teach_at = reinterpret_cast<float*>(static_cast<char*>(h->dmem) + total);
+    e = wn_teach_pack(L, R, S, h->dmem_f32 ? h->w_chain : h->w, teach_at, &h->teach);
     if (e != hipSuccess) {
       wn_destroy(h);
-      return e == hipErrorOutOfMemory ? fail(WN_ENOMEM, "hipMalloc of teacher forcing's weights")
-                                      : hip_fail(e, "packing teacher forcing's weights");
+      return hip_fail(e, "packing teacher forcing's weights");
     }
     h->teach_ok = true;
   }
@@ -738,7 +740,6 @@ void wn_destroy(wn_handle* h) {
     if (h->dmem) (void)hipFree(h->dmem);
     if (h->dpack) (void)hipFree(h->dpack);
     if (h->dmem_f32) (void)hipFree(h->dmem_f32);
-    if (h->dteach) (void)hipFree(h->dteach);
     if (h->abort_host) (void)hipHostFree(h->abort_host);
   }
   delete h;

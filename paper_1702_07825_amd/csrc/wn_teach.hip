@@ -203,13 +203,23 @@ struct Frag {
   }
 };
 
-// [rows][K] row-major to tiles of 16 rows by 16 inputs, lane order (rows a multiple of 16).
-__global__ __launch_bounds__(256) void pack_tiles(const float* src, float* dst, int rows, int K) {
-  const size_t i = (size_t)blockIdx.x * 256 + threadIdx.x;  // 16-byte piece of dst
-  if (i >= (size_t)rows * K / 4) return;
-  const int lane = i & 63, kt = (int)((i >> 6) % (K / 16));
-  const size_t rt = (i >> 6) / (K / 16);
-  st4(dst + 4 * i, ldg4(src + (16 * rt + (lane & 15)) * K + 16 * kt + 4 * (lane >> 4)));
+// [rows][K] row-major to tiles of 16 rows by 16 inputs, lane order (rows a multiple of 16); a matrix per
+// blockIdx.y.
+struct PackArgs {
+  struct {
+    const float* src;
+    float* dst;
+    size_t rows;
+    int K;
+  } m[6];
+};
+__global__ __launch_bounds__(256) void pack_tiles(const PackArgs a) {
+  const auto& m = a.m[blockIdx.y];
+  for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < m.rows * m.K / 4; i += (size_t)gridDim.x * 256) {  // 16-byte pieces of dst
+    const int lane = i & 63, kt = (int)((i >> 6) % (m.K / 16));
+    const size_t rt = (i >> 6) / (m.K / 16);
+    st4(m.dst + 4 * i, ldg4(m.src + (16 * rt + (lane & 15)) * m.K + 16 * kt + 4 * (lane >> 4)));
+  }
 }
 
 // acc[i][k] += W[channel tile i] . X[row tile k]: x[k] is row n of the tile at input 4 quad, in LDS.
@@ -1052,12 +1062,13 @@ hipError_t wn_teach_pack(int L, int R, int S, const WnDevWeights& w, float* dst,
       {w.w_prev, &out->prev, (size_t)L * 2 * R, R}, {w.w_cur, &out->cur, (size_t)L * 2 * R, R},
       {w.w_res, &out->res, (size_t)L * R, R},       {w.w_skip, &out->skip, (size_t)L * S, R},
       {w.w_relu, &out->relu, (size_t)A, S},         {w.w_out, &out->out, (size_t)A, A}};
-  for (const auto& x : m) {
-    hipLaunchKernelGGL(pack_tiles, dim3((unsigned)((x.rows * x.K / 4 + 255) / 256)), dim3(256), 0, nullptr,
-                       static_cast<const float*>(x.src), dst, (int)x.rows, x.K);
-    *x.at = dst;
-    dst += x.rows * x.K;
+  PackArgs a;
+  for (int k = 0; k < 6; ++k) {
+    a.m[k] = {static_cast<const float*>(m[k].src), dst, m[k].rows, m[k].K};
+    *m[k].at = dst;
+    dst += m[k].rows * m[k].K;
   }
+  hipLaunchKernelGGL(pack_tiles, dim3(256, 6), dim3(256), 0, nullptr, a);
   const hipError_t e = hipGetLastError();
   return e == hipSuccess ? hipStreamSynchronize(nullptr) : e;
 }
