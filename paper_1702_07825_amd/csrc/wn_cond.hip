@@ -28,6 +28,7 @@ struct wn_cond {
   int cinp1 = 0, cinp2 = 0;  // per-tap input widths of the two layers rounded up to 32
   void* dmem = nullptr;
   const unsigned short *w1 = nullptr, *w2 = nullptr;  // split (see split3)
+  const float *wf1 = nullptr, *wf2 = nullptr;         // what they are split from
   const float *b1 = nullptr, *b2 = nullptr;
   void* scratch = nullptr;  // device address of this device's copy of `scratch` (wn_condition_static)
 };
@@ -47,6 +48,7 @@ using wnk::u32x4;
 struct GateArgs {
   const float* x;  // [B][Tf][cin]
   const u16* w;    // [2][N][2 cinp / 32][3][32]: split weights; tap 0 (previous frame) inputs 0..cin-1, tap 1 at cinp.., zeros past cin
+  const float* wf; // [2][N][2 cinp]: the fp32 weights
   const float* b;  // [2][N]
   float* p;        // [B][Tf][2][N]
   int B, Tf, cin, cinp, N;
@@ -54,8 +56,10 @@ struct GateArgs {
 
 // fp32 products on bf16 MFMA.  A value is split into three bf16 parts, each the nearest to what the ones
 // before leave, v = h + m + l to 2^-25 of it, and a product takes the six of the nine part products that
-// reach fp32's precision (the others are below 2^-26 of it), smallest first, summed in fp32.  Infinities
-// stay in h alone.
+// reach fp32's precision (the others are below 2^-26 of it), smallest first, summed in fp32.  An infinity
+// stays in h alone, but its products with the other side's parts can be of both signs or with a zero part,
+// and a value within 2^-9 of fp32's largest has no finite h: such a sum ends as NaN and is taken again in
+// fp32 (exact_gate).
 __device__ __forceinline__ void split3(f32x4 v, uint2& h, uint2& m, uint2& l) {
   h = make_uint2(wnk::pack_bf16(v[0], v[1]), wnk::pack_bf16(v[2], v[3]));
   const float hv[4] = {wnk::low_bf16(h.x), wnk::high_bf16(h.x), wnk::low_bf16(h.y), wnk::high_bf16(h.y)};
@@ -77,6 +81,18 @@ __global__ __launch_bounds__(256) void split_weights(const float* src, u16* dst,
   *reinterpret_cast<uint2*>(d) = h;
   *reinterpret_cast<uint2*>(d + 32) = m;
   *reinterpret_cast<uint2*>(d + 64) = l;
+}
+
+// One gate pre-activation (row n, direction dir, frame m) in plain fp32, without the bias.
+__device__ __forceinline__ float exact_gate(const GateArgs& a, int dir, int n, int m) {
+  const int bb = m / a.Tf, t = m - bb * a.Tf, tp = dir == 0 ? t - 1 : t + 1;
+  const float* xc = a.x + (size_t)m * a.cin;
+  const bool has = tp >= 0 && tp < a.Tf;
+  const float* xp = has ? a.x + ((size_t)bb * a.Tf + tp) * a.cin : xc;
+  const float* w = a.wf + ((size_t)dir * a.N + n) * 2 * a.cinp;
+  float s = 0.f;
+  for (int k = 0; k < a.cin && s == s; ++k) s = fmaf(w[a.cinp + k], xc[k], fmaf(w[k], has ? xp[k] : 0.f, s));
+  return s;
 }
 
 // Gate pre-activations of every frame of a layer, both directions (grid.z):
@@ -207,7 +223,14 @@ __global__ __launch_bounds__(NTG, 2) void qrnn_gate_gemm(const GateArgs a) {
       const int m = m0 + wm + 16 * j + r16;
       if (m >= M) continue;
       float* dst = a.p + ((size_t)m * 2 + dir) * N + n;
-      const f32x4 v4 = acc[i][j] + bias;
+      f32x4 v4 = acc[i][j] + bias;
+      if (v4[0] != v4[0] || v4[1] != v4[1] || v4[2] != v4[2] || v4[3] != v4[3]) {
+#pragma unroll 1
+        for (int v = 0; v < 4 && n + v < N; ++v) {
+          const float e = exact_gate(a, dir, n + v, m) + bd[n + v];
+          v4 = f32x4{v == 0 ? e : v4[0], v == 1 ? e : v4[1], v == 2 ? e : v4[2], v == 3 ? e : v4[3]};
+        }
+      }
       if (whole) {
         *reinterpret_cast<f32x4*>(dst) = v4;
       } else {
@@ -357,9 +380,9 @@ class DeviceScope {
   bool ok_ = false;
 };
 
-hipError_t run_layer(const float* x, int B, int Tf, int cin, int cinp, int H, const u16* w, const float* b,
-                     float* p, float* out, int interleave, hipStream_t st) {
-  GateArgs g{x, w, b, p, B, Tf, cin, cinp, 3 * H};
+hipError_t run_layer(const float* x, int B, int Tf, int cin, int cinp, int H, const u16* w, const float* wf,
+                     const float* b, float* p, float* out, int interleave, hipStream_t st) {
+  GateArgs g{x, w, wf, b, p, B, Tf, cin, cinp, 3 * H};
   const bool vx = cin % 4 == 0 && reinterpret_cast<uintptr_t>(x) % 16 == 0;
   // 128 x 128 tiles where they fill the chip twice (two blocks share a CU), else 64 x 64: one
   // stream of 256 frames, second layer, 120 blocks of 128 x 128 on fp32 MFMA 85 us, 480 of 64 x 64 41 us.
@@ -412,8 +435,8 @@ int run_condition(wn_cond* c, int B, int n_frames, const float* features, int T,
   float* p = reinterpret_cast<float*>(ws + l.p_off);
   float* z1 = reinterpret_cast<float*>(ws + l.z1_off);
   float* cf = reinterpret_cast<float*>(ws + l.c_off);
-  hipError_t e = run_layer(features, B, n_frames, c->F, c->cinp1, c->h1, c->w1, c->b1, p, z1, 0, st);
-  if (e == hipSuccess) e = run_layer(z1, B, n_frames, 2 * c->h1, c->cinp2, c->h2, c->w2, c->b2, p, cf, 1, st);
+  hipError_t e = run_layer(features, B, n_frames, c->F, c->cinp1, c->h1, c->w1, c->wf1, c->b1, p, z1, 0, st);
+  if (e == hipSuccess) e = run_layer(z1, B, n_frames, 2 * c->h1, c->cinp2, c->h2, c->w2, c->wf2, c->b2, p, cf, 1, st);
   if (e == hipSuccess) {
     const int C = 2 * c->h2;
     const bool wide = C % 4 == 0 && reinterpret_cast<uintptr_t>(cond) % 16 == 0;
@@ -520,6 +543,8 @@ int wn_cond_create(const wn_cond_config* cfg, const wn_cond_weights* w, wn_cond*
   }
   c->w1 = reinterpret_cast<const u16*>(d);
   c->w2 = reinterpret_cast<const u16*>(d + o_w2);
+  c->wf1 = reinterpret_cast<const float*>(d + o_f);
+  c->wf2 = c->wf1 + w1p.size();
   c->b1 = reinterpret_cast<const float*>(d + o_b1);
   c->b2 = reinterpret_cast<const float*>(d + o_b2);
   *out = c;

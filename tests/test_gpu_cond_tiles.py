@@ -42,3 +42,32 @@ def test_conditioning_tiles(case):
         print("  stream %d max|dcond| = %.3g" % (b, err), flush=True)
         assert err <= 2e-5
     net.close()
+
+
+@pytest.mark.parametrize("F,h1,L,r,B,Tf", [(227, 48, 2, 16, 2, 40), (36, 32, 2, 32, 1, 70), (64, 256, 20, 64, 5, 221)],
+                         ids=["scalar_loads", "vector_loads", "tiles128"])
+def test_infinite_and_largest_values(F, h1, L, r, B, Tf):
+    """Infinities and fp32's largest value, in the features and in the weights: the sum of a gate is then infinite
+    or beyond 1e30 of one sign (one such term per sum), so the gates saturate and every output stays within the
+    bound above.  Split into parts, such a value would meet products of both signs."""
+    import paper_1702_07825_amd as wn
+    rng = np.random.default_rng(11)
+    top = np.finfo(np.float32).max
+    x = rng.normal(0, 1, (B, Tf, F)).astype(np.float32)
+    plain = synth.make_cond_weights(F, h1, L * r, seed=3, bias_scale=0.2)
+    x_odd = x.copy()
+    for i, t in enumerate(range(1, Tf, 3)):  # a width-2 window sees one of them
+        x_odd[:, t, (5 * i) % F] = (np.inf, -np.inf, top, -top)[i % 4]
+    w_odd = {k: v.copy() for k, v in plain.items()}
+    for i, n in enumerate(range(0, 3 * h1, 5)):
+        w_odd["w1"][i % 2, n, 1, (3 * i) % F] = (np.inf, -np.inf, top, -top)[i // 2 % 4]
+    for name, w, xs in (("features", plain, x_odd), ("weights", w_odd, x)):
+        net = wn.Conditioner(w, L, r, 1, 1)
+        got = net(torch.tensor(xs, device="cuda"), Tf).cpu().numpy().reshape(B, Tf, 2 * L * r)
+        net.close()
+        for b in sorted({0, B - 1}):
+            ref = oracle.condition(w, xs[b], Tf, 1, 1)
+            assert np.isfinite(ref).all()
+            err = float(np.abs(got[b] - ref).max())
+            print("  odd %s stream %d max|dcond| = %.3g" % (name, b, err), flush=True)
+            assert err <= 2e-5
