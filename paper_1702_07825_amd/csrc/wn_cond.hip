@@ -58,8 +58,8 @@ struct GateArgs {
 // before leave, v = h + m + l to 2^-25 of it, and a product takes the six of the nine part products that
 // reach fp32's precision (the others are below 2^-26 of it), smallest first, summed in fp32.  An infinity
 // stays in h alone, but its products with the other side's parts can be of both signs or with a zero part,
-// and a value within 2^-9 of fp32's largest has no finite h: such a sum ends as NaN and is taken again in
-// fp32 (exact_gate).
+// a value within 2^-9 of fp32's largest has no finite h, and a product within 2^-8 of it can be an infinity
+// as h h alone: such a sum ends as NaN or infinite and is taken again in fp32 (exact_gate).
 __device__ __forceinline__ void split3(f32x4 v, uint2& h, uint2& m, uint2& l) {
   h = make_uint2(wnk::pack_bf16(v[0], v[1]), wnk::pack_bf16(v[2], v[3]));
   const float hv[4] = {wnk::low_bf16(h.x), wnk::high_bf16(h.x), wnk::low_bf16(h.y), wnk::high_bf16(h.y)};
@@ -224,7 +224,7 @@ __global__ __launch_bounds__(NTG, 2) void qrnn_gate_gemm(const GateArgs a) {
       if (m >= M) continue;
       float* dst = a.p + ((size_t)m * 2 + dir) * N + n;
       f32x4 v4 = acc[i][j] + bias;
-      if (v4[0] != v4[0] || v4[1] != v4[1] || v4[2] != v4[2] || v4[3] != v4[3]) {
+      if (!__builtin_isfinite(v4[0]) || !__builtin_isfinite(v4[1]) || !__builtin_isfinite(v4[2]) || !__builtin_isfinite(v4[3])) {
 #pragma unroll 1
         for (int v = 0; v < 4 && n + v < N; ++v) {
           const float e = exact_gate(a, dir, n + v, m) + bd[n + v];

@@ -71,3 +71,31 @@ def test_infinite_and_largest_values(F, h1, L, r, B, Tf):
             err = float(np.abs(got[b] - ref).max())
             print("  odd %s stream %d max|dcond| = %.3g" % (name, b, err), flush=True)
             assert err <= 2e-5
+
+
+@pytest.mark.parametrize("F,h1,L,r,B,Tf", [(227, 48, 2, 16, 2, 40), (36, 32, 2, 32, 1, 70), (64, 256, 20, 64, 5, 221)],
+                         ids=["scalar_loads", "vector_loads", "tiles128"])
+def test_products_near_the_largest_value(F, h1, L, r, B, Tf):
+    """Products just below fp32's largest value (0.997 x 2^128, exact in 24 bits) whose operands round up to 2^64 as
+    bf16, cancelled by two products of half the size: the sum is 0 in any order, while the bf16 parts' product alone is
+    infinite (and the cancelling ones are finite, so no NaN tells)."""
+    import paper_1702_07825_amd as wn
+    v = np.float32(2045.0 / 1024.0 * 2.0 ** 63)
+    w = synth.make_cond_weights(F, h1, L * r, seed=5, bias_scale=0.2)
+    x = np.random.default_rng(13).normal(0, 1, (B, Tf, F)).astype(np.float32)
+    x[:, ::3, 1:4] = v
+    for c in range(0, h1, 5):  # the channel's h~ is the three terms alone; its o and f only their biases
+        w["b1"][:, c] = 0.0
+        for gate in range(3):
+            w["w1"][:, c + gate * h1] = 0.0
+        w["w1"][:, c, 1, 1:4] = (v, -v / 2, -v / 2)
+    x[:, 1::3, 1:4] = x[:, 2::3, 1:4] = 0.0  # (elsewhere the three terms would saturate the gate either way)
+    net = wn.Conditioner(w, L, r, 1, 1)
+    got = net(torch.tensor(x, device="cuda"), Tf).cpu().numpy().reshape(B, Tf, 2 * L * r)
+    net.close()
+    for b in sorted({0, B - 1}):
+        ref = oracle.condition(w, x[b], Tf, 1, 1)
+        assert np.isfinite(ref).all()
+        err = float(np.abs(got[b] - ref).max())
+        print("  stream %d max|dcond| = %.3g" % (b, err), flush=True)
+        assert err <= 2e-5
