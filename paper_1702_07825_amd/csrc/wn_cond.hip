@@ -251,13 +251,17 @@ struct PoolArgs {
 // fo-pool h_t = f_t h_{t-1} + (1 - f_t) tanh(a_h), z_t = sigmoid(a_o) h_t, over the frames in the
 // direction's own order.  The recurrence is linear in h, so the frames go in segments of PU, a thread
 // each: it runs its segment from h = 0, keeping the gates in registers, the segments' (product of f, end
-// value) chain through LDS, and it runs it again from where the segment before ends.  32 channels by
-// PS segments per block; longer sequences take further passes of PS segments.  Bound: the reads of p; a
+// value) chain through LDS, and it runs it again from where the segment before ends.  PC channels by
+// PS segments of PU frames per block; longer sequences take further passes of PS segments.  Sequences of up to
+// 16, 4 and 1 frames are one segment of 16, 4 and 1 (2048 streams of one frame, l = 20, r = 64, with 8 segments
+// of 16: 829 us a call, 480 with a thread per channel, 334 so).  Bound: the reads of p; a
 // thread per channel over all frames took 37 us for one stream of 256 frames, the loads' latency
 // sixteen times, so 6.8;
 // 32 streams of 512, 1280 channels: 262 -> 185 us.
-constexpr int PC = 32, PS = 8, PU = 16;
-__global__ __launch_bounds__(PC * PS) void qrnn_pool(const PoolArgs a) {
+constexpr int NTP = 256;
+template <int PS, int PU>
+__global__ __launch_bounds__(NTP) void qrnn_pool(const PoolArgs a) {
+  constexpr int PC = NTP / PS;
   __shared__ float s_f[PS][PC], s_h[PS][PC];
   const int c = threadIdx.x % PC, seg = threadIdx.x / PC;
   const int k = blockIdx.x * PC + c;
@@ -398,7 +402,14 @@ hipError_t run_layer(const float* x, int B, int Tf, int cin, int cinp, int H, co
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   PoolArgs pa{p, out, B, Tf, H, interleave};
-  hipLaunchKernelGGL(qrnn_pool, dim3((unsigned)((H + PC - 1) / PC), (unsigned)(2 * B)), dim3(PC * PS), 0, st, pa);
+  auto pool = [&](auto kernel, int segments) {
+    const int pc = NTP / segments;
+    hipLaunchKernelGGL(kernel, dim3((unsigned)((H + pc - 1) / pc), (unsigned)(2 * B)), dim3(NTP), 0, st, pa);
+  };
+  if (Tf <= 1) pool(qrnn_pool<1, 1>, 1);
+  else if (Tf <= 4) pool(qrnn_pool<1, 4>, 1);
+  else if (Tf <= 16) pool(qrnn_pool<1, 16>, 1);
+  else pool(qrnn_pool<8, 16>, 8);
   return hipGetLastError();
 }
 

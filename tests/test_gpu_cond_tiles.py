@@ -1,6 +1,6 @@
 """The conditioning network at the sizes where its kernels turn: the contraction's 128 x 128 tiles (from 512
 blocks on, ragged in frames and gate rows) beside the 64 x 64 ones, the pool's passes of 128 frames in
-segments of 16 (one frame more and less), and an output whose rows end inside a block's run of 1024 pieces.
+segments of 16 (one frame more and less) and its single segments of short sequences, and an output whose rows end inside a block's run of 1024 pieces.
 
 Against the oracle (64-bit): the split bf16 products keep fp32's precision, so a gate pre-activation of up to
 1024 terms with standard deviation near 1 is off by about 1024^(1/2) x 2^-24 = 2e-6, and the outputs, bounded by
@@ -22,6 +22,13 @@ CASES = [
     ("seg128", 36, 40, 2, 19, 2, 128, 3, 8, 1.0),
     ("seg129", 36, 40, 2, 19, 2, 129, 3, 8, 1.0),
     ("seg257_wide", 64, 32, 2, 32, 1, 257, 256, 16000, 1.0),
+    # short sequences: one segment of 1, 4 or 16 frames and 256 channels to a block, and the first that takes more
+    ("seg1", 36, 300, 2, 19, 3, 1, 1, 3, 1.0),
+    ("seg2", 36, 40, 2, 150, 2, 2, 3, 8, 1.0),
+    ("seg4", 36, 40, 2, 150, 2, 4, 3, 8, 1.0),
+    ("seg5", 36, 300, 2, 19, 2, 5, 3, 8, 1.0),
+    ("seg16", 36, 40, 2, 150, 2, 16, 3, 8, 1.0),
+    ("seg17", 36, 40, 2, 150, 2, 17, 3, 8, 1.0),
     ("saturated", 227, 48, 2, 16, 2, 40, 1, 1, 2.0 ** 60),
 ]
 
