@@ -461,15 +461,24 @@ __global__ __launch_bounds__(256) void teach_begin(const WnTeachArgs g, const Ch
 }
 
 // A progress word: tile i has read every input of the layers before j once prog[i] >= j.  Waits are
-// bounded; a block that gives up stores WN_ETIMEOUT, the others see the status.
+// bounded; a block that gives up stores WN_ETIMEOUT, the others see the status.  The polls count only once
+// every block runs (its progress word is 1 or more): while kernels of other streams hold CUs, some blocks
+// may start seconds after the others.  (The words are read only then: a count of the blocks that have
+// started, one atomic add each, made every launch 3 us longer.)
 __device__ __forceinline__ unsigned ld_prog(const WnTeachArgs& g, int tile) {
   return __hip_atomic_load(g.prog + tile * kProgStride, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 __device__ __forceinline__ bool gave_up(const WnTeachArgs& g, int& spins, int* fail) {
-  if (++spins <= g.spin_limit &&
-      ((spins & 63) != 0 || __hip_atomic_load(g.status, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0))
-    return false;
-  atomicCAS(g.status, 0, (int)WN_ETIMEOUT);
+  if (++spins <= g.spin_limit && (spins & 63) != 0) return false;
+  if (__hip_atomic_load(g.status, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0) {
+    if (spins <= g.spin_limit) return false;
+    for (int k = (int)gridDim.x - 1; k >= 0; --k)
+      if (ld_prog(g, k) == 0) {
+        spins = 0;
+        return false;
+      }
+    atomicCAS(g.status, 0, (int)WN_ETIMEOUT);
+  }
   *fail = 1;
   return true;
 }
@@ -671,29 +680,42 @@ __global__ __launch_bounds__(64 * pass_waves(R), pass_blocks(R)) void teach_pass
         w[k][0] = ld_words(xr, at);
         w[k][1] = ld_words(xr, at + 2);
       }
+      auto put = [&](const Piece& p, f32x4 v) {
+        if (g.ring_kind == WN_RING_PAIR) v = as_pair(v);
+        st4(Xp + p.lm * P + p.c, v);
+      };
+      auto here = [&](const u32x4 (&x)[2]) {
+        const unsigned tag = (unsigned)(j + 1);
+        return x[0][1] == tag && x[0][3] == tag && x[1][1] == tag && x[1][3] == tag;
+      };
+      auto value = [&](const u32x4 (&x)[2]) {
+        return f32x4{__uint_as_float(x[0][0]), __uint_as_float(x[0][2]), __uint_as_float(x[1][0]), __uint_as_float(x[1][2])};
+      };
+      unsigned late = 0;  // pieces that were not there yet
 #pragma unroll
       for (int k = 0; k < NI; ++k) {
         const Piece p = piece(k);
         if (p.t >= rg.d && p.in) {
           const int m = p.m - rg.d;
-          f32x4 v;
-          if (m >= m0) {
-            v = *reinterpret_cast<const f32x4*>(Xn + (m - m0) * P + p.c);
-          } else {
-            const unsigned at = base + (unsigned)m * R + p.c, tag = (unsigned)(j + 1);
-            int spins = 0;
-            while (w[k][0][1] != tag || w[k][0][3] != tag || w[k][1][1] != tag || w[k][1][3] != tag) {
-              if (gave_up(g, spins, &s_fail)) break;
-              asm volatile("" ::: "memory");  // (the loads stay in the loop)
-              w[k][0] = ld_words(xr, at);
-              w[k][1] = ld_words(xr, at + 2);
-            }
-            v = f32x4{__uint_as_float(w[k][0][0]), __uint_as_float(w[k][0][2]), __uint_as_float(w[k][1][0]), __uint_as_float(w[k][1][2])};
-          }
-          if (g.ring_kind == WN_RING_PAIR) v = as_pair(v);
-          st4(Xp + p.lm * P + p.c, v);
+          if (m >= m0) put(p, *reinterpret_cast<const f32x4*>(Xn + (m - m0) * P + p.c));
+          else if (here(w[k])) put(p, value(w[k]));
+          else late |= 1u << k;
         }
       }
+#pragma unroll 1
+      for (int k = 0; late >> k != 0; ++k)
+        if (late >> k & 1) {
+          const Piece p = piece(k);
+          const unsigned at = base + (unsigned)(p.m - rg.d) * R + p.c;
+          u32x4 x[2];
+          int spins = 0;
+          do {
+            asm volatile("" ::: "memory");  // (the loads stay in the loop)
+            x[0] = ld_words(xr, at);
+            x[1] = ld_words(xr, at + 2);
+          } while (!here(x) && !gave_up(g, spins, &s_fail));
+          put(p, value(x));
+        }
     }
   }
   lds_barrier();

@@ -10,6 +10,7 @@ up to 2e-6; int8 and bf16 models on exact weights alike); the bound is 1e-5.  Th
 hold two bf16 parts of a value (2^-17 of it, times sums over r = 64 of weights of 1/sqrt(2 r), over
 l layers): 1e-4.
 """
+import time
 import zlib
 
 import numpy as np
@@ -127,3 +128,62 @@ def test_chunks_of_a_long_call():
         b = net.teacher_force(cond[:, h:].contiguous(), y[:, h:].contiguous(), workspace=ws, reset=False)
         assert torch.equal(torch.cat([a, b], 1), whole)
     net.close()
+
+
+def test_timeout_path_drains_and_recovers(monkeypatch):
+    """The waits between tiles are bounded: with the host's spin limit forced to one poll a call of many tiles ends
+    with WN_ETIMEOUT (every block leaves, so the stream drains), and the next call from zero on the same
+    workspace gives the logits of an undisturbed one."""
+    import paper_1702_07825_amd as wn
+    L, r, s, B, T = 20, 64, 256, 2, 8000  # 500 tiles, two to a CU
+    net = wn.WaveNet(synth.make_weights(L, r, s, seed=9, bias_scale=0.1), tuple(synth.dilation_cycle(L)))
+    cond = synth.make_cond(L, r, B, T, seed=9, device="cuda")
+    y = torch.tensor(synth.make_samples(B, T, seed=9), device="cuda")
+    ws = net.new_workspace(B)
+    ref = net.teacher_force(cond, y)
+    monkeypatch.setenv("WN_SPIN_LIMIT", "1")
+    print("teacher forcing: forced timeout", flush=True)
+    net.teacher_force(cond, y, workspace=ws)
+    assert net.status(ws) == wn.WN_ETIMEOUT
+    monkeypatch.delenv("WN_SPIN_LIMIT")
+    assert torch.equal(net.teacher_force(cond, y, workspace=ws, reset=True), ref) and net.status(ws) == 0
+    net.close()
+
+
+def test_waits_while_another_stream_holds_compute_units(monkeypatch):
+    """A long kernel of another stream (192 workgroups, each filling a CU) keeps most of a call's 512 tiles off the chip
+    for many times the spin limit.  With a dilation of 256 tiles each tile that runs waits for one that does not:
+    the call finishes once all have run, and its logits are those of a call alone."""
+    import paper_1702_07825_amd as wn
+    L, r, s, T = 4, 16, 32, 16384
+    dil = (8192, 1, 2, 4)
+    w = synth.make_weights(L, r, s, seed=10, bias_scale=0.2)
+    net, other = wn.WaveNet(w, dil), wn.WaveNet(w, (1, 2, 4, 8))
+    assert net.kernel_variant(1) == "stream_l2"
+    cond = synth.make_cond(L, r, 1, T, seed=10, device="cuda")
+    y = torch.tensor(synth.make_samples(1, T, seed=10), device="cuda")
+    ref = net.teacher_force(cond, y)
+    BG, TG = 192, 16000
+    busy_cond = torch.zeros((BG, TG, L, 2 * r), device="cuda")
+    busy_u = torch.rand((BG, TG), device="cuda")
+    busy_ws, ws = other.new_workspace(BG), net.new_workspace(1)
+    out = torch.full((1, T, 256), -1.0, device="cuda")
+    side = torch.cuda.Stream()
+    other.generate(busy_cond[:, :100].contiguous(), busy_u[:, :100].contiguous(), workspace=busy_ws, stream=side)
+    torch.cuda.synchronize()
+    monkeypatch.setenv("WN_SPIN_LIMIT", "2000")  # about 2 ms of polls
+    print("teacher forcing beside a kernel that holds 192 CUs", flush=True)
+    t0 = time.perf_counter()
+    busy_y = other.generate(busy_cond, busy_u, workspace=busy_ws, stream=side)
+    time.sleep(0.004)  # it runs by now
+    net.teacher_force(cond, y, logits=out, workspace=ws)
+    status = net.status(ws)
+    took = time.perf_counter() - t0
+    assert other.status(busy_ws, stream=side) == 0
+    print("  status %d after %.1f ms, the other kernel's call took %.1f" % (status, 1e3 * took, 1e3 * (time.perf_counter() - t0)),
+          flush=True)
+    assert status == 0 and torch.equal(out, ref)
+    assert torch.equal(net.teacher_force(cond, y, workspace=ws, reset=True), ref) and net.status(ws) == 0
+    assert int(busy_y.min()) >= 0 and int(busy_y.max()) <= 255
+    net.close()
+    other.close()
