@@ -200,13 +200,20 @@ int spin_limit() {
 }
 
 // Teacher forcing takes every step of a call at once (wn_teach.hip) on a default handle; a handle that
-// WN_KERNEL binds to one family runs it there, step by step.
-bool teach_ok(const wn_handle* h) { return h->teach_ok; }
+// WN_KERNEL binds to one family runs it there, step by step.  So do batches that fill the chip on the
+// batched kernel: its step time hardly grows with the streams, and its bf16 products pass the fp32 ones
+// (calls of 250 steps at 800 / 1024 / 1400 / 2048 / 4096 streams, l = 20, r = 64, s = 256: 6.5 / 6.7 / 7.0 /
+// 7.5 / 9.3 ms step by step, 4.4 / 5.6 / 7.6 / 11.0 / 21.8 at once; l = 5, s = 128, 800 / 1600 streams: 2.0 /
+// 2.1 and 1.6 / 3.0).  The line depends on the batch alone: all calls on a state sum alike.
+constexpr int kTeachGroupStreams = 1100;
+bool teach_ok(const wn_handle* h, int B) {
+  return h->teach_ok && !(B >= kTeachGroupStreams && variant_for(h, B) == WN_VARIANT_GROUP);
+}
 
 // Its scratch lies behind the generator's state in the workspace.  A workspace that ends before it (no
 // larger than a handle bound to one family asks for) still serves every call, teacher forcing step by step.
 size_t teach_bytes(const wn_handle* h, int B) {
-  return teach_ok(h) ? align_up(wn_teach_scratch_bytes(h->R, B, WN_TEACH_ROWS), 256) : 0;
+  return teach_ok(h, B) ? align_up(wn_teach_scratch_bytes(h->R, B, WN_TEACH_ROWS), 256) : 0;
 }
 
 const wn_sampler kDirect = {WN_SAMPLE_DIRECT, 1.0f, WN_A};
@@ -290,7 +297,7 @@ int launch(wn_handle* h, int B, int T, const float* cond, const float* u, const 
   const WsLayout l = ws_layout(h, B);
   char* base = static_cast<char*>(ws);
   hipStream_t st = static_cast<hipStream_t>(stream);
-  if (teacher && teach_ok(h) && ws_bytes >= l.total + teach_bytes(h, B))
+  if (teacher && teach_ok(h, B) && ws_bytes >= l.total + teach_bytes(h, B))
     return launch_teach(h, B, T, cond, y_in, logits, l, base, reset, st);
   WnChainPlan plan;
   const int variant = variant_for(h, B);

@@ -187,3 +187,30 @@ def test_waits_while_another_stream_holds_compute_units(monkeypatch):
     assert int(busy_y.min()) >= 0 and int(busy_y.max()) <= 255
     net.close()
     other.close()
+
+
+@pytest.mark.parametrize("B", [1099, 1100])
+def test_batches_that_the_batched_kernel_forces_itself(B, monkeypatch):
+    """From 1100 streams on the batched kernel is the faster one and takes teacher forcing step by step, whatever a
+    call's length, in a workspace without the scratch; one stream fewer takes all steps of a call at once."""
+    import paper_1702_07825_amd as wn
+    L, r, s, T = 2, 64, 128, 18
+    w = synth.make_weights(L, r, s, seed=12, bias_scale=0.2)
+    net = wn.WaveNet(w, (1, 3), weight_dtype="bf16")
+    monkeypatch.setenv("WN_KERNEL", "mfma_group")
+    step = wn.WaveNet(w, (1, 3), weight_dtype="bf16")
+    monkeypatch.delenv("WN_KERNEL")
+    print("batched kernel's line, B=%d" % B, flush=True)
+    assert net.kernel_variant(B) == step.kernel_variant(B) == "mfma_group"
+    cond = synth.make_cond(L, r, B, T, seed=12, device="cuda")
+    y = torch.tensor(synth.make_samples(B, T, seed=12), device="cuda")
+    lg, ls = net.teacher_force(cond, y), step.teacher_force(cond, y)
+    own = B >= 1100
+    assert (net.workspace_bytes(B) == step.workspace_bytes(B)) == own and torch.equal(lg, ls) == own
+    assert float((lg - ls).abs().max()) <= 1e-4
+    ws = net.new_workspace(B)
+    parts = [net.teacher_force(cond[:, a:b].contiguous(), y[:, a:b].contiguous(), workspace=ws, reset=a == 0)
+             for a, b in ((0, 1), (1, T))]
+    assert torch.equal(torch.cat(parts, 1), lg) and net.status(ws) == 0
+    net.close()
+    step.close()
