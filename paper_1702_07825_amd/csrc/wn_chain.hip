@@ -1129,7 +1129,7 @@ size_t aux_lds_floats(int R, int S, int G, int nla) {
   const bool skl = R <= 64 ? aux_skip_in_lds<64>() : aux_skip_in_lds<128>();
   return (size_t)nla * ((size_t)R + (size_t)3 * R * G) + (skl ? (size_t)S * lds_row_stride(R, S / 64) + S : 0);
 }
-constexpr size_t kMaxLds = 160 * 1024;
+constexpr size_t kMaxLds = 160 * 1024 - 512;  // beside the kernel's static LDS (112 bytes)
 
 template <int R, int S>
 hipError_t launch_chain_rs(const WnChainArgs& g, bool teacher, hipStream_t stream) {

@@ -91,6 +91,28 @@ def test_multi_stream_chain_parity(case, monkeypatch):
     net.close()
 
 
+def test_most_streams_per_replica_at_r128(monkeypatch):
+    """At r = 128 an aux CU's LDS holds 14 streams of one layer (98 streams at l = 20); one more goes to the per-stream
+    kernel (15 would take all 160 KB and leave none for the kernel's static LDS)."""
+    import paper_1702_07825_amd as wn
+    L, r, s, T = 20, 128, 256, 3
+    dil = tuple(synth.dilation_cycle(L))
+    monkeypatch.setenv("WN_KERNEL", "multi_cu_chain")
+    w, net, cond, u, _ = _setup(L, r, s, dil, 99, T, seed=33, bias=0.2)
+    assert [net.kernel_variant(b) for b in (98, 99)] == ["multi_cu_chain", "stream_l2"]
+    y = torch.tensor(synth.make_samples(99, T, seed=33), device="cuda")
+    lg = {}
+    for B in (98, 99):
+        print("r = 128, B=%d" % B, flush=True)
+        ws = net.new_workspace(B)
+        net.generate(cond[:B].contiguous(), u[:B].contiguous(), workspace=ws)
+        assert net.status(ws) == 0
+        lg[B] = net.teacher_force(cond[:B].contiguous(), y[:B].contiguous(), workspace=ws)
+        assert net.status(ws) == 0
+    assert float((lg[98] - lg[99][:98]).abs().max()) <= 1e-4
+    net.close()
+
+
 def test_multi_stream_chain_state_and_placement():
     """Chunked calls continue exactly; results do not depend on which replica or slot serves a stream."""
     L, r, s, B, T = 20, 128, 256, 11, 260
