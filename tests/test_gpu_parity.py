@@ -14,6 +14,7 @@ import pytest
 
 import oracle
 import synth
+from tests.families import bound
 
 torch = pytest.importorskip("torch")
 pytestmark = pytest.mark.gpu
@@ -58,18 +59,21 @@ SMALL = [
 
 
 @pytest.mark.parametrize("case", SMALL, ids=[c[0] for c in SMALL])
-def test_logits_and_indices(case):
+def test_logits_and_indices(case, monkeypatch):
     name, L, r, s, dil, B, T, dtype, bias = case
     _log("case %s: L=%d r=%d s=%d B=%d T=%d %s" % (name, L, r, s, B, T, dtype))
     w, net, cond, u, model = _setup(L, r, s, dil, B, T, seed=zlib.crc32(name.encode()) % 1000, dtype=dtype, bias=bias)
     y = net.generate(cond, u)
-    lg = net.teacher_force(cond, y)
-    torch.cuda.synchronize()
-    y_np, lg_np = y.cpu().numpy(), lg.cpu().numpy()
+    own = bound(monkeypatch, net.kernel_variant(B), lambda: _wn().WaveNet(w, dil, weight_dtype=dtype))
+    assert own.kernel_variant(B) == net.kernel_variant(B)
+    # all steps at once, and step by step on the kernel that generates
+    lgs = [net.teacher_force(cond, y).cpu().numpy(), own.teacher_force(cond, y).cpu().numpy()]
+    own.close()
+    y_np = y.cpu().numpy()
     cond_np, u_np = cond.cpu().numpy(), u.cpu().numpy()
     assert y_np.min() >= 0 and y_np.max() <= 255
     ys, lo, mg = oracle.run_streams(model, cond_np, u=u_np, y_in=y_np, threads=8)
-    err = np.abs(lg_np - lo).max()
+    err = max(np.abs(lg_np - lo).max() for lg_np in lgs)
     ok = mg > MARGIN
     mism = int(np.sum(ys[ok] != y_np[ok]))
     _log("  max|dlogit|=%.3g low-margin steps=%d/%d mismatches=%d (low-margin disagreements %d)" %
@@ -79,7 +83,7 @@ def test_logits_and_indices(case):
     if dtype == "bf16":
         m32 = oracle.Model(w, dil)
         _, lo32, _ = oracle.run_streams(m32, cond_np, y_in=y_np, threads=8)
-        assert np.abs(lg_np - lo32).max() <= BF16_VS_F32_TOL
+        assert max(np.abs(lg_np - lo32).max() for lg_np in lgs) <= BF16_VS_F32_TOL
     # free-running agreement up to the first low-margin step of the oracle's own run
     for b in range(B):
         yo, _, mo = oracle.run(model, cond_np[b], u=u_np[b], want_logits=False)
@@ -88,7 +92,10 @@ def test_logits_and_indices(case):
     net.close()
 
 
-def test_chunked_equals_one_shot_and_determinism():
+@pytest.mark.parametrize("kernel", ["", "stream"], ids=["default", "stream"])
+def test_chunked_equals_one_shot_and_determinism(kernel, monkeypatch):
+    if kernel:
+        monkeypatch.setenv("WN_KERNEL", kernel)
     L, r, s, dil, B, T = 4, 16, 32, (1, 2, 4, 8), 3, 500
     w, net, cond, u, model = _setup(L, r, s, dil, B, T, seed=11, bias=0.3)
     y1 = net.generate(cond, u)
@@ -121,8 +128,11 @@ def test_stream_permutation():
     net.close()
 
 
-def test_edge_cases():
+@pytest.mark.parametrize("kernel", ["", "stream"], ids=["default", "stream"])
+def test_edge_cases(kernel, monkeypatch):
     wn = _wn()
+    if kernel:
+        monkeypatch.setenv("WN_KERNEL", kernel)
     L, r, s, dil = 4, 16, 32, (1, 2, 4, 8)
     w, net, cond, u, model = _setup(L, r, s, dil, 2, 1, seed=13, bias=0.2)
     # T = 1
@@ -145,8 +155,11 @@ def test_edge_cases():
     net.close()
 
 
-def test_initial_sample_and_bias_paths():
+@pytest.mark.parametrize("kernel", ["", "multi_cu_chain"], ids=["default", "multi_cu_chain"])
+def test_initial_sample_and_bias_paths(kernel, monkeypatch):
     """Non-default y_{-1} and nonzero biases everywhere."""
+    if kernel:
+        monkeypatch.setenv("WN_KERNEL", kernel)
     L, r, s, dil, B, T = 3, 64, 256, (1, 2, 4), 2, 64
     w, net, cond, u, model = _setup(L, r, s, dil, B, T, seed=14, bias=0.8, init=3)
     y = torch.tensor(synth.make_samples(B, T, seed=14), device="cuda")
@@ -185,11 +198,12 @@ def _whole_stream(w, dil, dtype, cb, ub, yb):
 
 
 @pytest.mark.parametrize("name", FULL)
-def test_full_size_sampled(name):
+def test_full_size_sampled(name, monkeypatch):
     """At the benchmark's full sizes, in the launch the benchmark times: every step of stream 0
     (the oracle replays the GPU's whole sample sequence, teacher-forced, past every wrap of the
     d = 512 histories), plus sampled steps of the last and the middle stream of a batch (each
-    checked on a window of sum(d) + 1 steps, the receptive field)."""
+    checked on a window of sum(d) + 1 steps, the receptive field).  Logits of teacher forcing at once and
+    step by step on the kernel that generates."""
     wl = synth.WORKLOADS[name]
     _log("full-size %s: %s" % (name, wl.description))
     w = synth.make_weights(wl.n_layers, wl.r, wl.s, seed=0, embed_taps=wl.embed_taps)
@@ -198,8 +212,12 @@ def test_full_size_sampled(name):
     cond = synth.make_cond(wl.n_layers, wl.r, wl.B, wl.T, seed=0, device="cuda")
     u = torch.tensor(synth.make_uniforms(wl.B, wl.T, seed=0), device="cuda")
     y = net.generate(cond, u)
-    lg = net.teacher_force(cond, y)
+    own = bound(monkeypatch, net.kernel_variant(wl.B),
+                lambda: wn.WaveNet(w, wl.dilations, weight_dtype=wl.weight_dtype))
+    assert own.kernel_variant(wl.B) == net.kernel_variant(wl.B)
+    lgs = [net.teacher_force(cond, y), own.teacher_force(cond, y)]
     torch.cuda.synchronize()
+    own.close()
     y_np = y.cpu().numpy()
     assert y_np.min() >= 0 and y_np.max() <= 255
     rng = np.random.default_rng(0)
@@ -208,20 +226,20 @@ def test_full_size_sampled(name):
         steps = sorted(set([wl.T - 1] + [int(x) for x in rng.integers(0, wl.T, 1)]))
         cb, ub = cond[b].cpu().numpy(), u[b].cpu().numpy()
         for t in steps:
-            jobs.append((b, t, cb, ub, lg[b, t].cpu().numpy()))
-    c0, u0, lg0 = cond[0].cpu().numpy(), u[0].cpu().numpy(), lg[0].cpu().numpy()
+            jobs.append((b, t, cb, ub, [lg[b, t].cpu().numpy() for lg in lgs]))
+    c0, u0 = cond[0].cpu().numpy(), u[0].cpu().numpy()
     with ThreadPoolExecutor(max_workers=8) as ex:
         whole = ex.submit(_whole_stream, w, wl.dilations, wl.weight_dtype, c0, u0, y_np[0])
         res = list(ex.map(lambda j: _window(w, wl.dilations, wl.weight_dtype, j[2], j[3], y_np[j[0]], j[1]), jobs))
         ys0, lo0, mg0 = whole.result()
-    worst0 = float(np.abs(lo0 - lg0).max())
+    worst0 = max(float(np.abs(lo0 - lg[0].cpu().numpy()).max()) for lg in lgs)
     ok0 = mg0 > MARGIN
     mism0 = int(np.sum(ys0[ok0] != y_np[0][ok0]))
     _log("  stream 0, all %d steps: max|dlogit|=%.3g confident=%d mismatches=%d" %
          (wl.T, worst0, int(ok0.sum()), mism0))
     worst, checked, mism = 0.0, 0, 0
     for (b, t, _, _, lg_bt), (lo, yo, mg) in zip(jobs, res):
-        worst = max(worst, float(np.abs(lo - lg_bt).max()))
+        worst = max([worst] + [float(np.abs(lo - x).max()) for x in lg_bt])
         if mg > MARGIN:
             checked += 1
             mism += int(yo != y_np[b, t])
@@ -311,6 +329,7 @@ def test_multi_cu_kernel_parity_and_state(L, S, monkeypatch):
     """Chain kernel vs oracle (logits, confident indices), chunked == one-shot, run twice == once."""
     r, T = 64, 400
     dil = tuple(synth.dilation_cycle(L))
+    monkeypatch.setenv("WN_KERNEL", "multi_cu_chain")  # teacher forcing on it too
     _log("multi-CU L=%d r=%d s=%d T=%d" % (L, r, S, T))
     w, net, cond, u, model = _setup(L, r, S, dil, 1, T, seed=L + S, bias=0.3)
     assert net.kernel_variant(1) == "multi_cu_chain"

@@ -36,6 +36,9 @@ CASES = [
     ("chain_bf16_b2", 6, (1, 2, 4, 8, 16, 32), 64, 256, 2, 90, "bf16", 1, False, "multi_cu_chain"),
     ("mfma_b37", 8, (1, 2, 4, 8, 16, 32, 64, 128), 64, 256, 170, 40, "bf16", 1, False, "multi_cu_mfma"),
     ("mfma_i8_t1", 8, (1, 2, 4, 8, 16, 32, 64, 128), 64, 256, 170, 1, "i8", 2, False, "multi_cu_mfma"),
+    # 16 streams per replica, one per tile column (WN_MFMA_COLUMNS), fewer in the last
+    ("mfma_16_columns", 5, (1, 2, 4, 8, 16), 64, 256, 67, 30, "bf16", 1, False, "multi_cu_mfma"),
+    ("mfma_16_columns_t3", 5, (1, 2, 4, 8, 16), 64, 256, 67, 3, "i8", 1, False, "multi_cu_mfma"),
     ("group_s128", 5, (1, 2, 4, 8, 16), 64, 128, 150, 25, "bf16", 1, False, "mfma_group"),
 ]
 
@@ -60,6 +63,8 @@ def test_teacher_forcing_parallel(case, monkeypatch):
     name, L, dil, r, s, B, T, dtype, taps, approx, family = case
     print("teacher forcing %s: L=%d r=%d s=%d B=%d T=%d %s" % (name, L, r, s, B, T, dtype), flush=True)
     seed = zlib.crc32(name.encode()) % 1000
+    if name.startswith("mfma_16_columns"):
+        monkeypatch.setenv("WN_MFMA_COLUMNS", "16")
     w = synth.make_weights(L, r, s, seed=seed, bias_scale=0.2, embed_taps=taps)
     net = wn.WaveNet(w, dil, weight_dtype=dtype, approx_nonlin=approx)
     assert net.kernel_variant(B) == family
@@ -92,6 +97,15 @@ def test_teacher_forcing_parallel(case, monkeypatch):
     # draws part where a uniform lies within that error of a CDF value: at most a few streams of a batch
     assert float((g0 != g2).any(1).float().mean()) <= (0.0 if B < 8 else 0.05)
 
+    # generation after a prompt forced from zero: as from the state the step kernel leaves, up to the same margin
+    after = []
+    for k in (net, step):
+        ws = k.new_workspace(B)
+        k.teacher_force(cond[:, :T].contiguous(), y, workspace=ws)
+        after.append(k.generate(cond[:, T:].contiguous(), u, workspace=ws, reset=False))
+        assert k.status(ws) == 0
+    assert float((after[0] != after[1]).any(1).float().mean()) <= (0.0 if B < 8 else 0.05)
+
     # a workspace without the scratch serves the call step by step
     ws = net.new_workspace(B)
     small = ws[:step.workspace_bytes(B)]
@@ -107,6 +121,43 @@ def test_teacher_forcing_parallel(case, monkeypatch):
     assert torch.equal(net.teacher_force(cond[:, :T].contiguous(), y, workspace=ws), lg) and net.status(ws) == 0
     net.close()
     step.close()
+
+
+TALL = [
+    # name, L, dilations, r, s, B, T, approx: rows just past where the tiles of a pass grow from 16 to 32 rows, and
+    # at r = 128 to 48 (one block per CU there: half the tiles)
+    ("r32", 3, (1, 40, 7), 32, 128, 1, 8193, False),
+    ("r64_s128", 3, (1, 33, 600), 64, 128, 2, 4100, False),
+    ("r64_s128_approx", 3, (1, 33, 600), 64, 128, 3, 2750, True),
+    ("r64", 3, (5, 1, 64), 64, 256, 1, 8193, False),
+    ("r128_32", 3, (1, 2, 100), 128, 256, 1, 4097, False),
+    ("r128_48", 3, (1, 2, 100), 128, 256, 1, 8193, False),
+    ("r128_48_approx", 2, (50, 1), 128, 256, 5, 1700, True),
+]
+
+
+@pytest.mark.parametrize("case", TALL, ids=[c[0] for c in TALL])
+def test_tall_tiles(case):
+    """The builds of a pass with tiles of 32 and 48 rows: against the oracle (bound as above), and bit for bit the
+    logits of calls short enough for tiles of 16."""
+    import paper_1702_07825_amd as wn
+    name, L, dil, r, s, B, T, approx = case
+    print("tall tiles %s" % name, flush=True)
+    w = synth.make_weights(L, r, s, seed=14, bias_scale=0.2)
+    net = wn.WaveNet(w, dil, approx_nonlin=approx)
+    cond = synth.make_cond(L, r, B, T, seed=14, device="cuda")
+    y = torch.tensor(synth.make_samples(B, T, seed=14), device="cuda")
+    lg = net.teacher_force(cond, y)
+    model = oracle.Model(w, dil, approx_nonlin=approx)
+    _, lo, _ = oracle.run_streams(model, cond.cpu().numpy(), y_in=y.cpu().numpy(), threads=5)
+    err = float(np.abs(lg.cpu().numpy() - lo).max())
+    print("  max|dlogit| oracle %.3g" % err, flush=True)
+    assert err <= 1e-5
+    ws, parts, n = net.new_workspace(B), [], 2048 // B
+    for a in range(0, T, n):
+        parts.append(net.teacher_force(cond[:, a:a + n].contiguous(), y[:, a:a + n].contiguous(), workspace=ws, reset=a == 0))
+    assert torch.equal(torch.cat(parts, 1), lg) and net.status(ws) == 0
+    net.close()
 
 
 def test_chunks_of_a_long_call():
@@ -147,6 +198,39 @@ def test_timeout_path_drains_and_recovers(monkeypatch):
     assert net.status(ws) == wn.WN_ETIMEOUT
     monkeypatch.delenv("WN_SPIN_LIMIT")
     assert torch.equal(net.teacher_force(cond, y, workspace=ws, reset=True), ref) and net.status(ws) == 0
+    net.close()
+
+
+def test_abort_between_the_chunks_of_a_call():
+    """A request made while a call of many chunks runs ends it at a chunk: the steps of the later ones are not
+    written, and the next call from zero on the same workspace is undisturbed."""
+    import paper_1702_07825_amd as wn
+    L, r, s, B, T = 20, 64, 256, 4, 150000
+    net = wn.WaveNet(synth.make_weights(L, r, s, seed=15, bias_scale=0.1), tuple(synth.dilation_cycle(L)))
+    cond = torch.zeros((B, T, L, 2 * r), device="cuda")
+    y = torch.tensor(synth.make_samples(B, 3000, seed=15), device="cuda").repeat(1, T // 3000)
+    ws = net.new_workspace(B)
+    ref = net.teacher_force(cond[:, :500].contiguous(), y[:, :500].contiguous())
+    out = torch.empty((B, T, 256), device="cuda")
+    net.teacher_force(cond, y, logits=out, workspace=ws)
+    assert net.status(ws) == 0
+    t0 = time.perf_counter()
+    net.teacher_force(cond, y, logits=out, workspace=ws)
+    assert net.status(ws) == 0
+    full = time.perf_counter() - t0
+    out.fill_(-1.0)
+    torch.cuda.synchronize()
+    net.teacher_force(cond, y, logits=out, workspace=ws)
+    time.sleep(0.2 * full)
+    net.abort(True)
+    status = net.status(ws)
+    net.abort(False)
+    written = (out[0, :, 0] != -1.0).sum().item()
+    print("  a whole call takes %.1f ms; aborted after %d of %d steps" % (1e3 * full, written, T), flush=True)
+    assert status == wn.WN_EABORTED
+    assert bool((out[:, -1] == -1.0).all())
+    again = net.teacher_force(cond[:, :500].contiguous(), y[:, :500].contiguous(), workspace=ws, reset=True)
+    assert torch.equal(again, ref) and net.status(ws) == 0
     net.close()
 
 

@@ -6,6 +6,7 @@ Sample indices must be the oracle's wherever its CDF margin (the rule's own marg
 Cases: one and the most layers it takes (8; with 9 the per-stream kernel serves), dilations of 1, 2 and
 longer than the call, a batch, two taps, each weight format, calls split at odd steps and across the
 64-step staging of the uniforms, each sampling rule, the approximate nonlinearities."""
+import time
 import zlib
 
 import numpy as np
@@ -85,3 +86,59 @@ def test_tiny_generation(case, monkeypatch):
     assert torch.equal(net.generate(cond, u, workspace=ws, sampler=smp), y) and net.status(ws) == 0
     net.close()
     ref.close()
+
+
+def _kernels(call):
+    """Names of the kernels that call() launches."""
+    from torch.profiler import ProfilerActivity, profile
+    call()
+    torch.cuda.synchronize()
+    with profile(activities=[ProfilerActivity.CUDA]) as prof:
+        call()
+        torch.cuda.synchronize()
+    return " ".join(e.key for e in prof.key_averages())
+
+
+@pytest.mark.parametrize("L,tiny", [(8, True), (9, False)])
+def test_the_kernel_that_runs(L, tiny):
+    """Up to 8 layers generation runs the kernel with resident weights, beyond the per-stream one (wn_kernel_variant
+    names the family, and with it the state's layout, for both)."""
+    import paper_1702_07825_amd as wn
+    net = wn.WaveNet(synth.make_weights(L, 16, 32, seed=2), (1, 2, 4, 8, 1, 2, 4, 8, 16)[:L])
+    cond = synth.make_cond(L, 16, 2, 20, seed=2, device="cuda")
+    u = torch.tensor(synth.make_uniforms(2, 20, seed=2), device="cuda")
+    ran = _kernels(lambda: net.generate(cond, u))
+    print("  kernels: %s" % ran, flush=True)
+    assert ("wn_tiny_kernel" in ran) == tiny and ("wn_stream_kernel" in ran) == (not tiny)
+    net.close()
+
+
+def test_abort_during_a_call():
+    """A request made while a call runs stops it within 64 steps; the next call from zero is undisturbed."""
+    import paper_1702_07825_amd as wn
+    L, B, T = 4, 2, 200000
+    net = wn.WaveNet(synth.make_weights(L, 16, 32, seed=6, bias_scale=0.1), (1, 2, 4, 8))
+    cond = synth.make_cond(L, 16, B, T, seed=6, device="cuda")
+    u = torch.tensor(synth.make_uniforms(B, T, seed=6), device="cuda")
+    ws = net.new_workspace(B)
+    ref = net.generate(cond[:, :200].contiguous(), u[:, :200].contiguous(), workspace=ws)
+    t0 = time.perf_counter()
+    net.generate(cond, u, workspace=ws)
+    assert net.status(ws) == wn.WN_OK
+    full = time.perf_counter() - t0
+    y = torch.full((B, T), -1, dtype=torch.int32, device="cuda")
+    torch.cuda.synchronize()
+    t0 = time.perf_counter()
+    net.generate(cond, u, samples=y, workspace=ws)
+    time.sleep(0.2 * full)
+    net.abort(True)
+    status = net.status(ws)
+    took = time.perf_counter() - t0
+    net.abort(False)
+    print("  a whole call takes %.1f ms; aborted after %.1f" % (1e3 * full, 1e3 * took), flush=True)
+    assert status == wn.WN_EABORTED and took < 0.8 * full
+    taken = [int((y[b] != -1).sum()) for b in range(B)]
+    assert all(n % 64 == 0 and bool((y[b, n:] == -1).all()) for b, n in enumerate(taken))
+    again = net.generate(cond[:, :200].contiguous(), u[:, :200].contiguous(), workspace=ws, reset=True)
+    assert torch.equal(again, ref) and net.status(ws) == wn.WN_OK
+    net.close()

@@ -14,6 +14,7 @@ import pytest
 
 import oracle
 import synth
+from tests.families import bound
 
 torch = pytest.importorskip("torch")
 pytestmark = pytest.mark.gpu
@@ -60,13 +61,15 @@ def test_two_tap_parity(case, monkeypatch):
     cond = synth.make_cond(L, r, B, T, seed=seed, device="cuda")
     u = torch.tensor(synth.make_uniforms(B, T, seed=seed), device="cuda")
     y = net.generate(cond, u)
-    lg = net.teacher_force(cond, y)
-    torch.cuda.synchronize()
-    y_np, lg_np = y.cpu().numpy(), lg.cpu().numpy()
+    # all steps at once (a default handle), and step by step on the kernel that generates
+    own = bound(monkeypatch, variant, lambda: _wn().WaveNet(w, dil, weight_dtype=dtype))
+    assert own.kernel_variant(B) == variant
+    lgs = [n.teacher_force(cond, y) for n in (net, own)]
+    y_np = y.cpu().numpy()
     model = oracle.Model(w, dil, bf16_weights=(dtype == "bf16"), int8_weights=(dtype == "i8"))
     assert model.receptive_field == 2 + sum(dil)
     ys, lo, mg = oracle.run_streams(model, cond.cpu().numpy(), u=u.cpu().numpy(), y_in=y_np, threads=8)
-    err = float(np.abs(lg_np - lo).max())
+    err = max(float(np.abs(lg.cpu().numpy() - lo).max()) for lg in lgs)
     ok = mg > MARGIN
     mism = int(np.sum(ys[ok] != y_np[ok]))
     print("  max|dlogit|=%.3g low-margin steps=%d/%d mismatches=%d" % (err, int((~ok).sum()), ok.size, mism),
@@ -81,11 +84,12 @@ def test_two_tap_parity(case, monkeypatch):
         y2 = net.generate(cond[:, split:].contiguous(), u[:, split:].contiguous(), workspace=ws, reset=False)
         torch.cuda.synchronize()
         assert torch.equal(torch.cat([y1, y2], 1), y), "split at %d" % split
-        ws = net.new_workspace(B)
-        l1 = net.teacher_force(cond[:, :split].contiguous(), y[:, :split].contiguous(), workspace=ws, reset=True)
-        l2 = net.teacher_force(cond[:, split:].contiguous(), y[:, split:].contiguous(), workspace=ws, reset=False)
-        torch.cuda.synchronize()
-        assert torch.equal(torch.cat([l1, l2], 1), lg), "teacher-forced split at %d" % split
+        for n, lg in zip((net, own), lgs):
+            ws = n.new_workspace(B)
+            l1 = n.teacher_force(cond[:, :split].contiguous(), y[:, :split].contiguous(), workspace=ws, reset=True)
+            l2 = n.teacher_force(cond[:, split:].contiguous(), y[:, split:].contiguous(), workspace=ws, reset=False)
+            torch.cuda.synchronize()
+            assert torch.equal(torch.cat([l1, l2], 1), lg), "teacher-forced split at %d" % split
 
     # E_prev = 0: the one-table model with E = E_cur, bit for bit
     w0 = dict(w)
@@ -94,9 +98,9 @@ def test_two_tap_parity(case, monkeypatch):
     w1 = dict(w)
     w1["embed"] = w["embed"][1].copy()
     n0, n1 = _net(w0, dil, dtype, kernel, monkeypatch), _net(w1, dil, dtype, kernel, monkeypatch)
-    assert n0.kernel_variant(B) == n1.kernel_variant(B) == variant
-    a_, b_ = n0.teacher_force(cond, y), n1.teacher_force(cond, y)
-    torch.cuda.synchronize()
-    assert torch.equal(a_, b_)
-    for n in (net, n0, n1):
+    o0, o1 = (bound(monkeypatch, variant, lambda: _wn().WaveNet(x, dil, weight_dtype=dtype)) for x in (w0, w1))
+    for a, b in ((n0, n1), (o0, o1)):
+        assert a.kernel_variant(B) == b.kernel_variant(B) == variant
+        assert torch.equal(a.teacher_force(cond, y), b.teacher_force(cond, y))
+    for n in (net, own, n0, n1, o0, o1):
         n.close()
