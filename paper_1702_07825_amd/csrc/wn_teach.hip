@@ -7,10 +7,10 @@
 // [s x r] of a tile in one kernel, on fp32 MFMA (v_mfma_f32_16x16x4f32) with every sum in fp32, whatever
 // the model's storage (bf16 weights are exact in fp32, int8 ones are code * scale rounded to fp32).
 //
-// A call runs in chunks of up to 16384 rows (256 tiles of 64, one per CU), each one launch of teach_pass,
-// which takes its tiles through all layers and the head; a call of at most kSmallT steps takes the
-// small_* kernels instead.  Both do a row's sums in the same order, so its logits do not depend on how a
-// sequence is cut into calls, chunks or tiles.
+// A call runs in chunks of up to 16384 rows (512 tiles of up to 32, two to a CU; at r = 128 12288 rows, 256
+// tiles of up to 48), each one launch of teach_pass, which takes its tiles through all layers and the head;
+// a call of at most kSmallT steps takes the small_* kernels instead.  Both do a row's sums in the same
+// order, so its logits do not depend on how a sequence is cut into calls, chunks or tiles.
 //
 // The dilation histories in the workspace are read and written in the layout of the kernel family that
 // generates with this handle and batch (ring_load, ring_store), so calls of either kind continue each
@@ -30,7 +30,7 @@ namespace {
 using namespace wnk;
 
 constexpr int A = WN_A;
-constexpr int kSmallT = 16;  // longest call that teach_small takes: one tile of rows
+constexpr int kSmallT = 16;  // longest call that the small_* kernels take: one tile of rows
 
 __device__ __forceinline__ f32x4 ldg4(const float* p) { return *reinterpret_cast<const f32x4*>(p); }
 __device__ __forceinline__ void st4(float* p, f32x4 v) { *reinterpret_cast<f32x4*>(p) = v; }
@@ -249,7 +249,7 @@ struct Layer {
   using G = Split<R, NC, W>;  // the gate (each channel tile with its sigmoid half) and the residual
   using K = Split<S, NC, W>;  // the skip projection
   // the gate's product [W_prev | W_cur] . [x[t - d] ; x[t]] goes in runs of KB inputs
-  static constexpr int KB = R < 64 ? R : (G::NRT > 1 ? 32 : 64), RUNS = 2 * R / KB;
+  static constexpr int KB = R < 64 ? R : 64, RUNS = 2 * R / KB;
   using GateFrag = Frag<KB, 2 * G::NRT>;
   struct ResFrag {
     Frag<R, G::NRT> w;
@@ -365,7 +365,7 @@ struct Layer {
 };
 
 // One of the head's products over a tile of 16 NC rows, W [A][K] by X [16 NC][pitch(K)] in LDS, its
-// weights streamed in runs of 64 inputs, one run ahead.
+// weights streamed in runs of 32 inputs, one run ahead.
 template <int K, int NC, int W>
 __device__ __forceinline__ void head_product(f32x4 (&acc)[A / 16 / W][NC], const float* w, const float* X, int wave) {
   constexpr int N = A / 16 / W, KB = 32;
@@ -425,9 +425,9 @@ __device__ __forceinline__ void head_tile(const WnTeachArgs& g, const float* Z, 
 }
 
 // A teach_pass block: four waves and tiles of 16 or 32 rows, two blocks to a CU, so that one block's products
-// run beside the other's exchange (16000 rows, l = 20, r = 64, s = 256: 345 us per call against 358 for one
-// block of eight waves and 64 rows).  At r = 128 a wave's
-// weights of a layer only fit its registers with eight waves: one block per CU, tiles of 16, 32 or 48 rows.
+// run beside the other's exchange (16000 rows, l = 20, r = 64, s = 256, when it was chosen: 345 us per call
+// against 358 for one block of eight waves and 64 rows; now 331).  At r = 128 a wave's weights of a layer
+// only fit its registers with eight waves: one block per CU, tiles of 16, 32 or 48 rows.
 constexpr int pass_waves(int R) { return R == 128 ? 8 : 4; }
 constexpr int pass_blocks(int R) { return R == 128 ? 1 : 2; }
 
@@ -496,7 +496,7 @@ __device__ __forceinline__ void wait_prog(const WnTeachArgs& g, int tile, unsign
 // slot until the row that read that has.  Every wait is for a lower layer, or for an earlier tile at the
 // same one, and the launch is cooperative (every block resident), so the waits end.
 // Bound: the fp32 matrix rate (73.7 KFLOP per row and layer at r = 64, s = 256).  Measured, l = 20, r = 64,
-// s = 256, one stream of 16000 steps: 330 us per call, 84 TFLOP/s (the step-by-step kernels took 178.8 ms);
+// s = 256, one stream of 16000 steps: 331 us per call, 84 TFLOP/s (the step-by-step kernels took 178.8 ms);
 // without any exchange (a timing build) 306.
 template <int R, int S, int NC, bool AX>
 __global__ __launch_bounds__(64 * pass_waves(R), pass_blocks(R)) void teach_pass(const WnTeachArgs g, const Chunk ch) {
@@ -747,16 +747,16 @@ __global__ __launch_bounds__(64 * pass_waves(R), pass_blocks(R)) void teach_pass
 // channels), all in the sums' order of teach_pass.
 // ------------------------------------------------------------------------------------------
 struct Small {
-  int b0, tiles;      // first stream; tiles of `per` streams
+  int tiles;          // of `per` streams
   float *pre, *h;     // [L][16 tiles][2R], [L][16 tiles][R]
   float *z, *za;      // [16 tiles][S] relu(q), [16 tiles][A]
 };
 // Row m of a tile: step m % T of its stream m / T.
 struct SmallTile {
   int b0, M;
-  __device__ SmallTile(const WnTeachArgs& g, const Small& s, int tile) {
+  __device__ SmallTile(const WnTeachArgs& g, int tile) {
     const int per = kSmallT / g.io.T;
-    b0 = s.b0 + tile * per;
+    b0 = tile * per;
     M = min(per, g.io.B - b0) * g.io.T;
   }
 };
@@ -777,7 +777,7 @@ __global__ __launch_bounds__(64) void small_pre(const WnTeachArgs g, const Small
     atomicCAS(g.status, 0, (int)WN_EABORTED);
   const int d = g.d.dil[j];
   if (d < T) return;
-  const SmallTile st(g, s, tile);
+  const SmallTile st(g, tile);
   const int lane = threadIdx.x, n = lane & 15, quad = lane >> 4, m = min(n, st.M - 1), t = m % T, b = st.b0 + m / T;
   const int64_t tg = g.io.reset ? 0 : g.state[WN_STATE_WORDS * (size_t)st.b0];
   const int slot = (int)((tg + t) % d);
@@ -815,7 +815,7 @@ __global__ __launch_bounds__(64 * small_waves(R), 1) void small_chain(const WnTe
   if (*g.status != 0) return;
   const int T = g.io.T, L = g.d.L, tid = threadIdx.x, tile = blockIdx.x;
   const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), n = lane & 15, quad = lane >> 4;
-  const SmallTile st(g, s, tile);
+  const SmallTile st(g, tile);
   const int M = st.M, b0 = st.b0;
   const GS gs(wave);
   const bool on = gs.on(0);
@@ -985,13 +985,156 @@ __global__ __launch_bounds__(64) void small_head(const WnTeachArgs g, const Smal
   mma_rows<K>(acc, w, x);
   f32x4 v = acc + b;
   if (LAST) {
-    const SmallTile st(g, s, tile);
+    const SmallTile st(g, tile);
     const int T = g.io.T;
     if (n < st.M) st4(g.io.logits + ((size_t)(st.b0 + n / T) * T + n % T) * A + c, v);
   } else {
 #pragma unroll
     for (int e = 0; e < 4; ++e) v[e] = fmaxf(v[e], 0.f);
     st4(s.za + ((size_t)tile * 16 + n) * A + c, v);
+  }
+}
+
+// The same at r = 16, where a CU reads a layer's weights in a fraction of its latency: one launch, a tile per
+// block.  Wave 0 runs the chain alone: with 16 channels the result layout of one product (lane (n, quad):
+// channels 4 quad .. of row n) is the operand layout of the next, so x and h stay in its registers, a row
+// looks back on another by a shuffle, and no barrier stands in the chain.  Then two waves take the skip sums
+// and all of them the head.  Bound: latencies, one after the other.  Measured, l = 4, one stream: 14.1 us a
+// call of one step, 14.3 of 16 (in the five launches above 24.6 and 24.5; on the per-stream kernel 12.2 and
+// 118).  Head weights loaded into registers beside the chain: 14.7, as fewer blocks share a CU.
+// More tiles go to teach_pass: l = 4, 512 tiles 49 against 53 us, 1024 tiles 85 against 68; l = 20 83 against
+// 118 and 147 against 135.
+constexpr int kOneWaves = 8, kOneTiles = 512;
+template <int R, int S, bool AX>
+__global__ __launch_bounds__(64 * kOneWaves, 4) void small_one(const WnTeachArgs g) {
+  static_assert(R == 16 && S == 32 && A == 256, "layouts below");
+  extern __shared__ __align__(16) float dyn[];
+  constexpr int PZ = pitch(S), DEEP = 2;
+  float* H = dyn;                   // [L][16][R] h of every layer
+  float* Z = H + g.d.L * 16 * R;    // [16][PZ] relu(q)
+  float* ZA = Z + 16 * PZ;          // [16][pitch(A)]
+  __shared__ int s_stop;
+  const int T = g.io.T, L = g.d.L;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), n = lane & 15, quad = lane >> 4;
+  const int c = 4 * quad;
+  const SmallTile st(g, blockIdx.x);
+  int64_t tg = 0;
+  if (wave == 0) {
+    struct Stage {
+      Frag<R, 2> wp, wc;
+      Frag<R, 1> wr;
+      f32x4 b[2], l[2], br, past;
+      int d;
+      float* slot;  // this lane's channels of the history slot its row reads
+    } stage[DEEP];
+    const int m = min(n, st.M - 1), t = m % T, b = st.b0 + m / T;
+    const bool mine = n < st.M;
+    const float* cond = g.io.cond + ((size_t)b * T + t) * L * 2 * R + c;
+    int64_t* const state = g.state + WN_STATE_WORDS * (size_t)st.b0;
+    tg = g.io.reset ? 0 : state[0];
+    const int tgm = (int)(tg % g.d.dil[min(lane, L - 1)]);  // of layer `lane`
+    float* const ring = static_cast<float*>(g.ring) + (size_t)b * g.d.hist_len + c;  // (WN_RING_F32)
+    auto fetch = [&](Stage& f, int j) {
+      auto pair = [&](int i) { return j * 2 * R + i * R; };
+      f.wp.load(g.p.prev, R, 0, pair);
+      f.wc.load(g.p.cur, R, 0, pair);
+      f.wr.load(g.p.res, R, 0, [&](int) { return j * R; });
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        f.b[i] = ldg4(g.w.b_gate + pair(i) + c);
+        f.l[i] = __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(cond + pair(i)));
+      }
+      f.br = ldg4(g.w.b_res + j * R + c);
+      f.d = g.d.dil[j];
+      const int v = __builtin_amdgcn_readlane(tgm, j) + t;  // below 2^17: see Piece
+      f.slot = ring + g.d.hoff[j] + (size_t)(v - (int)(((float)v + 0.5f) * (1.0f / (float)f.d)) * f.d) * R;
+      f.past = ldg4(f.slot);
+      issued();
+    };
+#pragma unroll
+    for (int k = 0; k < DEEP; ++k) fetch(stage[k], min(k, L - 1));
+    int4 start = make_int4(0, 0, g.io.init_sample, -1);
+    if (!g.io.reset) {
+      const int64_t* ps = g.state + WN_STATE_WORDS * (size_t)b;
+      start.z = (int)ps[1];
+      start.w = (int)ps[2];
+    }
+    f32x4 x = mine ? embed4(g, start, b, t, c) : zero4();
+    auto layer = [&](int j, Stage& f) {
+      f32x4 xp, acc[2] = {zero4(), zero4()};
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const float back = __shfl(x[e], (lane & 48) | ((n - f.d) & 15), 64);
+        xp[e] = t >= f.d ? back : f.past[e];
+      }
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+#pragma unroll
+        for (int i = 0; i < 2; ++i) acc[i] = __builtin_amdgcn_mfma_f32_16x16x4f32(f.wp.f[i][0][e], xp[e], acc[i], 0, 0, 0);
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+#pragma unroll
+        for (int i = 0; i < 2; ++i) acc[i] = __builtin_amdgcn_mfma_f32_16x16x4f32(f.wc.f[i][0][e], x[e], acc[i], 0, 0, 0);
+      const f32x4 ah = acc[0] + (f.b[0] + f.l[0]), ag = acc[1] + (f.b[1] + f.l[1]);
+      f32x4 h, res = zero4();
+#pragma unroll
+      for (int e = 0; e < 4; ++e) h[e] = tanh_nl<AX>(ah[e]) * sigmoid_nl<AX>(ag[e]);
+      st4(H + (j * 16 + n) * R + c, h);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) res = __builtin_amdgcn_mfma_f32_16x16x4f32(f.wr.f[0][0][e], h[e], res, 0, 0, 0);
+      // the history of layer j: the slot was read (by this wave, above) before row t of the last d writes it
+      if (mine && t + f.d >= T) st4(f.slot, x);
+      x = x + (res + f.br);
+      fetch(f, min(j + DEEP, L - 1));
+    };
+    for (int j = 0;;) {
+      layer(j, stage[0]);
+      if (++j == L) break;
+      layer(j, stage[1]);
+      if (++j == L) break;
+    }
+  } else if (wave == kOneWaves - 1) {
+    int stop = __hip_atomic_load(g.status, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0;
+    if (!stop && abort_requested(g.io.abort_flag)) {
+      stop = 1;
+      if (lane == 0) atomicCAS(g.status, 0, (int)WN_EABORTED);
+    }
+    if (lane == 0) s_stop = stop;
+  }
+  lds_barrier();
+  if (s_stop) return;
+  if (wave == 1 || wave == 2) {
+    const int ct = wave - 1;
+    f32x4 q = ldg4(g.w.b_skip + 16 * ct + c);
+    constexpr int U = 4;
+    for (int j0 = 0; j0 < L; j0 += U) {
+      Frag<R, 1> w[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) w[u].load(g.p.skip, R, 0, [&](int) { return min(j0 + u, L - 1) * S + 16 * ct; });
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        if (j0 + u >= L) break;
+        const f32x4 h = *reinterpret_cast<const f32x4*>(H + ((j0 + u) * 16 + n) * R + c);
+        f32x4 acc = zero4();
+#pragma unroll
+        for (int e = 0; e < 4; ++e) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(w[u].f[0][0][e], h[e], acc, 0, 0, 0);
+        q += acc;
+      }
+    }
+#pragma unroll
+    for (int e = 0; e < 4; ++e) q[e] = fmaxf(q[e], 0.f);
+    st4(Z + n * PZ + 16 * ct + c, q);
+  }
+  lds_barrier();
+  head_tile<S, 1, kOneWaves>(g, Z, ZA, [&](int m, int ch, f32x4 v) {
+    if (m < st.M) st4(g.io.logits + ((size_t)(st.b0 + m / T) * T + m % T) * A + ch, v);
+  });
+  if (wave == 0 && lane < st.M / T) {
+    int64_t* ps = g.state + WN_STATE_WORDS * (size_t)(st.b0 + lane);
+    const int32_t* y = g.io.y_in + (size_t)(st.b0 + lane) * T;
+    ps[2] = T >= 2 ? clamp_y(y[T - 2]) : (g.io.reset ? g.io.init_sample : ps[1]);
+    ps[1] = clamp_y(y[T - 1]);
+    ps[0] = tg + T;
   }
 }
 
@@ -1030,11 +1173,20 @@ hipError_t run_small(const WnTeachArgs& g, Small s, hipStream_t st) {
 template <int R, int S, bool AX>
 hipError_t run(const WnTeachArgs& g, hipStream_t st) {
   const int B = g.io.B, T = g.io.T, L = g.d.L;
-  if (T <= kSmallT) {
+  if constexpr (R == 16) {
+    const int tiles = T <= kSmallT ? (B + kSmallT / T - 1) / (kSmallT / T) : 0;
+    if (T <= kSmallT && tiles <= kOneTiles) {
+      const size_t lds = (size_t)16 * 4 * (L * R + pitch(S) + pitch(A));
+      const hipError_t e = with_lds(small_one<R, S, AX>, lds);
+      if (e != hipSuccess) return e;
+      hipLaunchKernelGGL((small_one<R, S, AX>), dim3(tiles), dim3(64 * kOneWaves), lds, st, g);
+      return hipGetLastError();
+    }
+  } else if (T <= kSmallT) {
     const size_t tile_floats = (size_t)16 * (L * 3 * R + S + A), have = (size_t)6 * g.rows * R;
     const int tiles = (B + kSmallT / T - 1) / (kSmallT / T);
     if (tiles * tile_floats <= have) {
-      Small s{0, tiles, g.x, nullptr, nullptr, nullptr};
+      Small s{tiles, g.x, nullptr, nullptr, nullptr};
       s.h = s.pre + (size_t)L * 16 * tiles * 2 * R;
       s.z = s.h + (size_t)L * 16 * tiles * R;
       s.za = s.z + (size_t)16 * tiles * S;

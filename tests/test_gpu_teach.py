@@ -27,6 +27,8 @@ CASES = [
     ("stream_tiny", 4, (1, 2, 4, 8), 16, 32, 3, 17, "f32", 1, False, "stream_l2"),
     ("stream_tiny_bf16", 4, (1, 2, 4, 8), 16, 32, 5, 100, "bf16", 2, False, "stream_l2"),
     ("stream_tiny_i8_t16", 3, (3, 1, 40), 16, 32, 2, 16, "i8", 1, False, "stream_l2"),
+    ("stream_l64_t5_b7", 64, tuple(synth.dilation_cycle(64)), 16, 32, 7, 5, "f32", 2, True, "stream_l2"),
+    ("stream_l1_t1", 1, (1,), 16, 32, 33, 1, "bf16", 1, False, "stream_l2"),
     ("chain_r32", 5, (1, 3, 9, 27, 81), 32, 128, 2, 333, "f32", 1, False, "multi_cu_chain"),
     ("chain_r64_s128", 6, (1, 2, 4, 8, 16, 64), 64, 128, 1, 65, "f32", 1, True, "multi_cu_chain"),
     ("chain_l20", 20, tuple(synth.dilation_cycle(20)), 64, 256, 1, 1300, "f32", 2, False, "multi_cu_chain"),
@@ -157,6 +159,28 @@ def test_tall_tiles(case):
     for a in range(0, T, n):
         parts.append(net.teacher_force(cond[:, a:a + n].contiguous(), y[:, a:a + n].contiguous(), workspace=ws, reset=a == 0))
     assert torch.equal(torch.cat(parts, 1), lg) and net.status(ws) == 0
+    net.close()
+
+
+@pytest.mark.parametrize("B", [1536, 1537])
+def test_short_calls_of_many_small_streams(B):
+    """r = 16: up to 512 tiles (of 3 streams at 5 steps) go in one launch, one more stream in a pass: the same logits
+    bit for bit, from zero and continued, as calls of a few of the streams."""
+    import paper_1702_07825_amd as wn
+    L, T = 3, 5
+    net = wn.WaveNet(synth.make_weights(L, 16, 32, seed=17, bias_scale=0.2), (1, 4, 9))
+    print("short calls, B=%d" % B, flush=True)
+    cond = synth.make_cond(L, 16, B, 2 * T, seed=17, device="cuda")
+    y = torch.tensor(synth.make_samples(B, 2 * T, seed=17), device="cuda")
+
+    def two(some):
+        c, yy, ws = cond[some].contiguous(), y[some].contiguous(), net.new_workspace(len(some))
+        out = [net.teacher_force(c[:, a:a + T].contiguous(), yy[:, a:a + T].contiguous(), workspace=ws, reset=a == 0)
+               for a in (0, T)]
+        assert net.status(ws) == 0
+        return torch.cat(out, 1)
+    whole, some = two(list(range(B))), [0, 1, 2, 3, B // 2, B - 2, B - 1]
+    assert torch.equal(whole[some], two(some))
     net.close()
 
 
