@@ -499,7 +499,7 @@ int wn_create(const wn_config* c, const wn_weights* w, wn_handle** out) {
     }
   }
   // The multi-CU kernels and teacher forcing need one CU per block (or two blocks) of their grids.
-  if (const char* force = std::getenv("WN_KERNEL")) h->force = force;
+  if (const char* force = std::getenv("WN_KERNEL")) h->force = std::strcmp(force, "stream_l2") ? force : "stream";
   int cus = 0, coop = 0, lds_max = 0;
   (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, h->device);
   (void)hipDeviceGetAttribute(&coop, hipDeviceAttributeCooperativeLaunch, h->device);
@@ -581,9 +581,9 @@ int wn_create(const wn_config* c, const wn_weights* w, wn_handle** out) {
   if (want_chain && wn_chain_supported(R, S, L) && cus >= WN_CHAIN_GRID && coop) h->chain_ok = true;
   if (want_chain && (bf || i8) && wn_mchain_supported(R, S, L) && cus >= WN_CHAIN_GRID && coop) h->mchain_ok = true;
   if (h->chain_ok || h->mchain_ok) h->xcd_map = wn_chain_xcd_map_ok();
-  if ((h->chain_ok || h->force.empty()) && (i8 || bf)) {
-    // fp32 copies of the matrices for the fp32 multi-CU kernel and for teacher forcing: each bf16 weight (exact in fp32), or each
-    // int8 code * scale, rounded to fp32 once here (the per-stream kernel multiplies its row sums by
+  if ((h->chain_ok || teach) && (i8 || bf)) {
+    // fp32 copies of the matrices for the fp32 multi-CU kernel and for teacher forcing: each bf16 weight (exact
+    // in fp32), or each int8 code * scale, rounded to fp32 once here (the per-stream kernel multiplies its row sums by
     // the scale instead)
     size_t ftotal = 0;
     std::vector<size_t> foff(7);

@@ -366,3 +366,13 @@ def test_multi_cu_kernel_parity_and_state(L, S, monkeypatch):
     assert float((lg_ref - lg).abs().max()) <= 1e-4
     ref.close()
     net.close()
+
+
+@pytest.mark.parametrize("name", ["stream", "stream_l2"])
+def test_per_stream_kernel_by_either_name(name, monkeypatch):
+    """WN_KERNEL takes the name that wn_kernel_variant returns for the per-stream kernel, and its short form, for a
+    model that another family would serve."""
+    monkeypatch.setenv("WN_KERNEL", name)
+    net = _wn().WaveNet(synth.make_weights(3, 64, 256, seed=1), (1, 2, 4))
+    assert [net.kernel_variant(b) for b in (1, 40)] == ["stream_l2"] * 2
+    net.close()
