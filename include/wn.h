@@ -40,7 +40,7 @@
  *  - Environment variables (tuning and tests; read at wn_create or at each call):
  *      WN_KERNEL=name        wn_create: serve every call with one kernel family (a name that
  *                            wn_kernel_variant returns; calls it cannot serve use stream_l2)
- *      WN_SPIN_LIMIT=n       each call: polls before a multi-CU wait gives up (wn_status)
+ *      WN_SPIN_LIMIT=n       each call: polls before a wait between CUs gives up (wn_status)
  *      WN_LOCAL_POSTS=0      each call: the multi-CU kernel writes every message through to
  *                            memory instead of stopping same-XCD messages at the XCD's L2
  *      WN_GROUP_STREAMS=8|16 each call: streams per workgroup of the batched bf16 kernel
@@ -168,8 +168,9 @@ int wn_create(const wn_config* config, const wn_weights* weights, wn_handle** ou
  * Bytes of device workspace one call with B streams needs: the generator state
  * of every stream (each layer's dilation history of r fp32 values per step of
  * its dilation, the step counter and the last two samples) plus a status word, and
- * the scratch of wn_teacher_force (25 MB at r = 64; a workspace without it is accepted
- * too, and teacher forcing then goes step by step).
+ * the scratch of wn_teacher_force where that takes the steps of a call at once (6 MB at
+ * r = 16, 25 MB at r = 64, 50 MB at r = 128, whatever B; a workspace without it is
+ * accepted too, and teacher forcing then goes step by step).
  * The layout is private.  Returns 0 for a null handle or B < 1.
  */
 size_t wn_workspace_bytes(const wn_handle* h, int32_t B);
@@ -208,7 +209,8 @@ int wn_generate_sampled(wn_handle* h, int32_t B, int32_t T, const float* cond, c
  *   logits  device fp32 [B][T][a] out
  * Other arguments and errors as wn_generate.  With the samples given no step waits for another, so a
  * call takes all of its steps through a layer at once (every sum in fp32; a sequence cut into calls
- * gives the logits of one call bit for bit).  With WN_KERNEL set it goes step by step on that family.
+ * gives the logits of one call bit for bit).  With WN_KERNEL set, or from 1100 streams on where the
+ * batched kernel serves them, it goes step by step on the family that generates.
  */
 int wn_teacher_force(wn_handle* h, int32_t B, int32_t T, const float* cond, const int32_t* y,
                      float* logits, void* workspace, size_t ws_bytes, int32_t reset, void* stream);
@@ -216,8 +218,10 @@ int wn_teacher_force(wn_handle* h, int32_t B, int32_t T, const float* cond, cons
 /*
  * Wait for `stream` and return the status word the kernels left in `workspace`:
  * WN_OK, WN_ETIMEOUT or WN_EABORTED; WN_EINVAL for null arguments; WN_EHIP if
- * the stream reports an error.  Blocks the calling thread.  The multi-CU kernel's
- * waits for other CUs give up after a bounded number of polls (a few seconds);
+ * the stream reports an error.  Blocks the calling thread.  The waits for other CUs, in the
+ * multi-CU kernels and in teacher forcing of more than 16 steps at once, give up after a bounded
+ * number of polls (a few seconds; teacher forcing counts them only while every workgroup of the
+ * launch runs, so another stream's long kernel delays it and does not end it);
  * the environment variable WN_SPIN_LIMIT, read at each call, sets that number
  * (tests force the timeout path with it).  After WN_ETIMEOUT or WN_EABORTED the
  * workspace state is stale: the next call must pass reset = 1.
@@ -234,7 +238,8 @@ int wn_status(wn_handle* h, const void* workspace, void* stream);
  * launch and stop at their first step; withdraw it before the next call, which must pass
  * reset = 1.  A call that has passed its last check finishes normally (status WN_OK).  A
  * wn_teacher_force call that takes its steps at once reads the word at the start of every 16384 rows
- * (streams x steps; a few hundred microseconds of work).
+ * (streams x steps; 12288 at r = 128): 0.35 ms of work at l = 20, r = 64, and in proportion to l and to
+ * r (2 r + r + s) for other models.
  * Errors: WN_EINVAL (null handle, on not 0 or 1).  Nothing is launched.
  */
 int wn_abort(wn_handle* h, int32_t on);

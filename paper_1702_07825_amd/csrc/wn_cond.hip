@@ -109,7 +109,7 @@ __device__ __forceinline__ float exact_gate(const GateArgs& a, int dir, int n, i
 // GFLOP) 2244 us on fp32 MFMA, 1359 so (207 TFLOP/s, 1.24 PFLOP/s of bf16 products, about what a large
 // bf16 matrix product reaches on the card); error against 64 bits 3.4e-7 and 3.2e-7 (of the whole network).
 constexpr int NTG = 256;
-constexpr int VK = 32, VLD = 3 * VK + 16;  // K chunk; LDS row (16-bit units): 32 bytes mod 64, free of bank conflicts
+constexpr int VK = 32, VLD = 3 * VK + 16;  // K chunk; LDS row (16-bit units): 32 bytes mod 64 (conflicts a quarter of the LDS cycles)
 
 template <int VT, bool VX>
 __global__ __launch_bounds__(NTG, 2) void qrnn_gate_gemm(const GateArgs a) {

@@ -407,7 +407,7 @@ int launch(wn_handle* h, int B, int T, const float* cond, const float* u, const 
     if (se != hipSuccess) return hip_fail(se, "status clear launch");
   }
   // Generation with the smallest models keeps the weights on the CU (l = 4, one stream: 2.8 against 7.3
-  // us/step); more layers do not fit its LDS.
+  // us/step); its static LDS arrays hold 8 layers (64 KB; the CU's 160 KB would take dynamic ones).
   const bool tiny = !teacher && h->force.empty() && wn_tiny_supported(h->R, h->S, h->L);
   const hipError_t e = tiny ? wn_tiny_launch(args, st) : wn_stream_launch(args, teacher, st);
   if (e != hipSuccess) return hip_fail(e, "kernel launch");

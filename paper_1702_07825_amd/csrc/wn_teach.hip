@@ -495,7 +495,8 @@ __device__ __forceinline__ void wait_prog(const WnTeachArgs& g, int tile, unsign
 // tile waits until the tiles that read it have (their progress words), and before it overwrites a history
 // slot until the row that read that has.  Every wait is for a lower layer, or for an earlier tile at the
 // same one, and the launch is cooperative (every block resident), so the waits end.
-// Bound: the fp32 matrix rate (73.7 KFLOP per row and layer at r = 64, s = 256).  Measured, l = 20, r = 64,
+// Bound: the fp32 matrix units (73.7 KFLOP per row and layer at r = 64, s = 256), busy 54 % of the cycles, and
+// the latencies between a layer's products.  Measured, l = 20, r = 64,
 // s = 256, one stream of 16000 steps: 331 us per call, 84 TFLOP/s (the step-by-step kernels took 178.8 ms);
 // without any exchange (a timing build) 306.
 template <int R, int S, int NC, bool AX>
@@ -1193,7 +1194,10 @@ hipError_t run(const WnTeachArgs& g, hipStream_t st) {
       return run_small<R, S, AX>(g, s, st);
     }
   }
-  // chunks of up to `rows` rows: whole calls of as many streams as fit, or else runs of steps
+  // Chunks of up to `rows` rows: whole calls of as many streams as fit, or else runs of steps, at least 256 of a
+  // stream.  Full chunks cost the same with runs of 64 to 1024 steps; what differs is the short launches that a
+  // call's remainder adds (100 streams of 1000 steps, l = 20, r = 64: 2.68 ms, 2.17 with runs of 1024; 32 of 1500
+  // at r = 128: 2.39 and 2.70), so no one length is best.
   const int rows = std::min(g.rows, WN_TEACH_TILES / 2 * pass_blocks(R) * (R == 128 ? 48 : 32));
   const int steps = std::min(T, rows);
   const int nb = std::max(1, std::min(B, rows / std::min(steps, 256)));
