@@ -1005,7 +1005,11 @@ __global__ __launch_bounds__(64) void small_head(const WnTeachArgs g, const Smal
 // 118).  Head weights loaded into registers beside the chain: 14.7, as fewer blocks share a CU.
 // More tiles go to teach_pass: l = 4, 512 tiles 49 against 53 us, 1024 tiles 85 against 68; l = 20 83 against
 // 118 and 147 against 135.
-constexpr int kOneWaves = 8, kOneTiles = 512;
+//
+// Tile t is block t + 4: block b runs on XCD b mod 8, and a single stream's generation, one block, on XCD 0.
+// There its tile's weights, another copy of the matrices, would take from that L2 what the generating calls
+// between keep there (three voices in turn, l = 4, 1600 steps and one forced: 4.58 ms a turn on XCD 0, 4.43 so, 4.52 in five launches).
+constexpr int kOneWaves = 8, kOneTiles = 512, kOneFirst = 4;
 template <int R, int S, bool AX>
 __global__ __launch_bounds__(64 * kOneWaves, 4) void small_one(const WnTeachArgs g) {
   static_assert(R == 16 && S == 32 && A == 256, "layouts below");
@@ -1018,7 +1022,8 @@ __global__ __launch_bounds__(64 * kOneWaves, 4) void small_one(const WnTeachArgs
   const int T = g.io.T, L = g.d.L;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), n = lane & 15, quad = lane >> 4;
   const int c = 4 * quad;
-  const SmallTile st(g, blockIdx.x);
+  if ((int)blockIdx.x < kOneFirst) return;
+  const SmallTile st(g, blockIdx.x - kOneFirst);
   int64_t tg = 0;
   if (wave == 0) {
     struct Stage {
@@ -1180,7 +1185,7 @@ hipError_t run(const WnTeachArgs& g, hipStream_t st) {
       const size_t lds = (size_t)16 * 4 * (L * R + pitch(S) + pitch(A));
       const hipError_t e = with_lds(small_one<R, S, AX>, lds);
       if (e != hipSuccess) return e;
-      hipLaunchKernelGGL((small_one<R, S, AX>), dim3(tiles), dim3(64 * kOneWaves), lds, st, g);
+      hipLaunchKernelGGL((small_one<R, S, AX>), dim3(tiles + kOneFirst), dim3(64 * kOneWaves), lds, st, g);
       return hipGetLastError();
     }
   } else if (T <= kSmallT) {
