@@ -496,9 +496,9 @@ __device__ __forceinline__ void wait_prog(const WnTeachArgs& g, int tile, unsign
 // slot until the row that read that has.  Every wait is for a lower layer, or for an earlier tile at the
 // same one, and the launch is cooperative (every block resident), so the waits end.
 // Bound: the fp32 matrix units (73.7 KFLOP per row and layer at r = 64, s = 256), busy 54 % of the cycles, and
-// the latencies between a layer's products.  Measured, l = 20, r = 64,
-// s = 256, one stream of 16000 steps: 331 us per call, 84 TFLOP/s (the step-by-step kernels took 178.8 ms);
-// without any exchange (a timing build) 306.
+// the latencies between a layer's products.  Measured, l = 20, r = 64, s = 256, one stream of 16000 steps:
+// 331 us per call, 84 TFLOP/s (the step-by-step kernels took 178.8 ms); without any exchange (a timing
+// build) 306.
 template <int R, int S, int NC, bool AX>
 __global__ __launch_bounds__(64 * pass_waves(R), pass_blocks(R)) void teach_pass(const WnTeachArgs g, const Chunk ch) {
   extern __shared__ __align__(16) float dyn[];
@@ -1002,13 +1002,14 @@ __global__ __launch_bounds__(64) void small_head(const WnTeachArgs g, const Smal
 // looks back on another by a shuffle, and no barrier stands in the chain.  Then two waves take the skip sums
 // and all of them the head.  Bound: latencies, one after the other.  Measured, l = 4, one stream: 14.1 us a
 // call of one step, 14.3 of 16 (in the five launches above 24.6 and 24.5; on the per-stream kernel 12.2 and
-// 118).  Head weights loaded into registers beside the chain: 14.7, as fewer blocks share a CU.
-// More tiles go to teach_pass: l = 4, 512 tiles 49 against 53 us, 1024 tiles 85 against 68; l = 20 83 against
-// 118 and 147 against 135.
+// 118).  (With the head's weights loaded into registers beside the chain: 14.7, and one block to a CU.)
+// More than kOneTiles tiles go to teach_pass: l = 4, 512 tiles 49 against 53 us, 1024 tiles 85 against 68;
+// l = 20 83 against 118 and 147 against 135.
 //
 // Tile t is block t + 4: block b runs on XCD b mod 8, and a single stream's generation, one block, on XCD 0.
 // There its tile's weights, another copy of the matrices, would take from that L2 what the generating calls
-// between keep there (three voices in turn, l = 4, 1600 steps and one forced: 4.58 ms a turn on XCD 0, 4.43 so, 4.52 in five launches).
+// between keep there (three voices in turn, l = 4, 1600 steps and one forced: 4.58 ms a turn on XCD 0, 4.43
+// so, 4.52 in five launches).
 constexpr int kOneWaves = 8, kOneTiles = 512, kOneFirst = 4;
 template <int R, int S, bool AX>
 __global__ __launch_bounds__(64 * kOneWaves, 4) void small_one(const WnTeachArgs g) {
